@@ -611,8 +611,8 @@ struct Prefill {
 
   // Whole tiles after a wave's first one (SM 1 with P.V) take the relative
   // form in kernels with a bias or cap: every row of the wave has seen a key
-  // by then (its own causal diagonal, or the whole first tile), so its
-  // reference is finite.
+  // by then (the kernel counts the tile of a row's first key as masked unless
+  // it is the wave's first tile), so its reference is finite.
   static constexpr bool rel(int SM, bool PV) { return LOG2 && SM == 1 && PV; }
 
   // The 2 NG MFMA slots of one iteration.  Slot 2 i: S^T MFMA with K fragment
@@ -808,6 +808,17 @@ __global__ __launch_bounds__(kThreads, kWgPerCu) __attribute__((amdgpu_num_vgpr(
       b = (hi(wlast) + BN - 1) / BN;
       wl = (lo(wlast) + BN - 1) / BN;
       wh = hi(it.iw) / BN;
+      // With a bias or cap, whole tiles after the first visible one take the
+      // relative form, which needs every row's reference to be finite.  The
+      // last row to see a key (the wave's last row at the window's lower
+      // edge, its first row where the keys run backward from the diagonal)
+      // may see none of the first tile; the tile in which it sees its first
+      // key then counts as masked even where every row sees all of it.
+      if (PF::LOG2 && WIN && !REV && lo(wlast) / BN > a) wl = lo(wlast) / BN + 1;
+      if (PF::LOG2 && CAUSAL && REV && hi(it.iw) > 0) {
+        const int t = (hi(it.iw) - 1) / BN;
+        if (t < b - 1) wh = min(wh, t);
+      }
     }
     if (REV) {
       it.f0 = it.t1 - b;  it.f1 = it.t1 - 1 - a;
