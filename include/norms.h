@@ -46,10 +46,12 @@ typedef enum {
 
 /*
  * Chunks per row that norm_l2 (rms = 0) or rmsnorm_rowmax (rms != 0) uses
- * when `chunks` is 0: 1 when the N rows fill at least 85 % of ceil(N / CUs)
- * rounds of the current device's compute units (so N >= CUs) and, for
- * RMSNorm, a row has at most 256 KiB (M * element size <= 262144): one
- * workgroup per row, RMSNorm reading X once.  Otherwise about 512 workgroups
+ * when `chunks` is 0.  1 (one kernel, a wave or a workgroup per row, RMSNorm
+ * reading X once) when a row has at most 64 KiB; when it has at most 208 KiB
+ * and N is at least half the compute units of the current device; or when the
+ * N rows fill at least 85 % of ceil(N / CUs) rounds of the compute units (so
+ * N >= CUs) and, for RMSNorm, a row has at most 256 KiB (M * element size <=
+ * 262144).  Otherwise about 512 workgroups
  * in all with chunks of at least 4096 elements.  Without a device the CU
  * count is taken as 256.  Returns >= 1, or 0 for invalid sizes.
  */
@@ -81,7 +83,8 @@ size_t norm_workspace_bytes(int N, int chunks);
  * heuristic; the chunk size is ceil(M / chunks) rounded up to whole 16-byte
  * vectors, so trailing chunks may be short or empty.  Two kernels run: the
  * chunk partials, then the per-row combine; with one chunk per row, one
- * kernel (a workgroup per row writes the row's partial and its norm).
+ * kernel (a wave or a workgroup per row writes the row's partial and its
+ * norm).
  */
 int norm_l2(const void* X, float* out, int N, int M, norm_dtype dtype, int chunks,
             void* workspace, size_t workspace_bytes, hipStream_t stream);
@@ -91,9 +94,9 @@ int norm_l2(const void* X, float* out, int N, int M, norm_dtype dtype, int chunk
  * weight, and rowmax[n] (fp32) = max of row n of the unrounded Y.  eps >= 0,
  * finite.  Two kernels run: the statistics of every chunk in one pass over
  * X, then a kernel that combines each row's partials and writes Y.  With one
- * chunk per row and rows of at most 256 KiB, one kernel runs instead: a
- * workgroup per row holds the row in registers, writes the row's partial and
- * its row max, and writes Y from the registers (X is read once).
+ * chunk per row and rows of at most 256 KiB, one kernel runs instead: a wave
+ * or a workgroup per row holds the row in registers, writes the row's partial
+ * and its row max, and writes Y from the registers (X is read once).
  */
 int rmsnorm_rowmax(const void* X, void* Y, float* rowmax, int N, int M, float eps, norm_dtype dtype,
                    int chunks, void* workspace, size_t workspace_bytes, hipStream_t stream);

@@ -301,15 +301,24 @@ size_t peaks_mfma_operand_bytes(void) { return attn::mfma_loop_operand_bytes(); 
 
 int norm_chunks(int rms, int N, int M, norm_dtype dtype) {
   if (N < 1 || M < 1 || (dtype != NORM_F16 && dtype != NORM_BF16 && dtype != NORM_F32)) return 0;
-  // One chunk per row (one kernel, a workgroup per row) when the rows fill at
-  // least 85 % of the compute units' rounds and, for RMSNorm, a row fits the
-  // workgroup's registers (X is then read once; that workgroup takes a whole
-  // compute unit).  On the 256 x 2^17 workloads, from HBM: the one-pass
-  // RMSNorm ran 1.19x the two kernels with 2 chunks, the L2 norm's one-chunk
-  // kernel 1.03x its two chunks.
-  const int64_t elem = dtype == NORM_F32 ? 4 : 2, cu = compute_units();
+  // One chunk per row means one kernel (a wave or a workgroup per row), X
+  // read once.  It pays when
+  //  - a row has at most 64 KiB: a row's time in one workgroup is then below
+  //    that of a second kernel (64 x 32768 bf16 RMSNorm 4.1 us, 5.9 with 8
+  //    chunks; L2 64 x 16384 fp32 3.9 against 5.1; at 128 KiB 7.8 against
+  //    6.7 for 64 rows);
+  //  - half the compute units have a row of at most 208 KiB, the longest
+  //    measured (RMSNorm 128 x 50000 fp32 11.9 us against 13.9, 400 x 100000
+  //    bf16 30 against 43; L2 150 x 50000 fp32 8.7 against 9.3);
+  //  - the rows fill at least 85 % of the compute units' rounds and, for
+  //    RMSNorm, a row fits the workgroup's registers (256 x 2^17: RMSNorm
+  //    1.19x the two kernels with 2 chunks, the L2 norm 1.03x; but L2 300 x
+  //    2^17 fp32 31 us against 29 with 2 chunks).
+  const int64_t elem = dtype == NORM_F32 ? 4 : 2, cu = compute_units(), row = M * elem;
   const int64_t rounds = (N + cu - 1) / cu;
-  if (attn::norm_one_kernel(rms != 0, M, (int)elem, 1) && N >= cu && (int64_t)N * 100 >= rounds * cu * 85) return 1;
+  if (attn::norm_one_kernel(rms != 0, M, (int)elem, 1) &&
+      (row <= 65536 || (2 * (int64_t)N >= cu && row <= 212992) || (N >= cu && (int64_t)N * 100 >= rounds * cu * 85)))
+    return 1;
   // Otherwise about two workgroups per compute unit (measured on the 256 x
   // 2^17 row reductions: 2 chunks per row beat 4, 8 and 16), chunks of at
   // least 4096 elements.

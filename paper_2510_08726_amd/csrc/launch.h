@@ -97,13 +97,14 @@ struct NormParams {
   int rms;              // 1: RMSNorm with row max, 0: L2 norm
   float eps;
   float invM;           // 1 / M
+  int lanes;            // lanes per row of the row kernels, set by the launcher
 };
 hipError_t launch_norm(const NormParams& p, hipStream_t stream);
 // Longest row (bytes) that RMSNorm with one chunk per row holds in the
 // registers of one workgroup (1024 lanes x 16 vectors of 16 bytes), reading X once.
 constexpr long long kNormRowBytes = 1024LL * 16 * 16;
 // True when a row reduction with `chunks` chunks per row runs one kernel
-// (one workgroup per row: the L2 norm always, RMSNorm when the row fits)
+// (a wave or a workgroup per row: the L2 norm always, RMSNorm when the row fits)
 // rather than the chunk partials and a second kernel.
 inline bool norm_one_kernel(bool rms, long long M, int elem, int chunks) {
   return chunks == 1 && (!rms || M * elem <= kNormRowBytes);
