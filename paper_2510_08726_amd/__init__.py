@@ -1,11 +1,16 @@
 """Fused attention for AMD Instinct MI355X (gfx950) — Python binding of libattn.so.
 
-A thin ctypes layer over the C ABI declared in ``include/attn.h``: the
-functions below have the same names as the C entry points and only marshal
-arguments (device pointers, sizes, the current HIP stream).  Every step of the
+A thin layer over the C ABI declared in ``include/attn.h``: the functions
+below have the same names as the C entry points and only marshal arguments
+(device pointers, sizes, the current HIP stream).  Every step of the
 computation runs in the HIP kernels of ``libattn.so``; PyTorch only provides
 device memory and streams.  There is no fallback: if the library is missing
 or a call fails, an exception is raised.
+
+A plainly valid call on the current stream is marshalled in C++
+(``csrc/binding.cpp``, the ``_binding`` module), whose functions return None
+for anything else: the call then goes through the checks below, which raise
+the errors, and ctypes.
 """
 
 import ctypes
@@ -36,6 +41,7 @@ _DTYPE_CODE = {torch.float16: ATTN_F16, torch.bfloat16: ATTN_BF16}
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB = None
+_BINDING = None
 
 
 class AttnError(RuntimeError):
@@ -108,6 +114,33 @@ def load_library():
     return lib
 
 
+class _NotBuilt:
+    """Stands for the _binding module where nothing is built: every call goes
+    through the checks in Python and then load_library's error."""
+
+    @staticmethod
+    def _none(*args):
+        return None
+
+    attn_fwd = attn_decode = attn_decode_noalloc = norm_l2 = rmsnorm_rowmax = _none
+
+
+def _load_binding():
+    """Load (once) the _binding module; raises if only libattn.so is built."""
+    global _BINDING
+    if not os.path.exists(library_path()):
+        return _NotBuilt
+    load_library()
+    try:
+        from . import _binding as b
+    except ImportError as e:
+        raise RuntimeError(
+            f"{os.path.join(_HERE, '_binding.so')} is not built for this PyTorch; run "
+            "`python -c 'import __graft_entry__ as g; g.build()'` first") from e
+    _BINDING = b
+    return b
+
+
 def attn_status_string(status):
     return load_library().attn_status_string(int(status)).decode()
 
@@ -122,6 +155,13 @@ def _check(rc):
         if rc == ATTN_ERR_HIP:
             msg += f" (hipError_t {attn_last_hip_error()})"
         raise AttnError(rc, msg)
+
+
+def _result(r):
+    """What a _binding function returned: the output, or an error status (int)."""
+    if type(r) is int:
+        _check(r)
+    return r
 
 
 def _ptr(t):
@@ -173,6 +213,9 @@ def attn_fwd(q, k, v, o=None, *, causal=False, scale=None, alibi_slopes=None, so
     select the score modifiers of ``attn_fwd_mod``; without them the call
     goes to the C entry point ``attn_fwd``.  Returns ``o``.
     """
+    r = (_BINDING or _load_binding()).attn_fwd(q, k, v, o, causal, scale, alibi_slopes, softcap, window, stream)
+    if r is not None:
+        return _result(r)
     if softcap or window:
         return attn_fwd_mod(q, k, v, o, causal=causal, scale=scale, alibi_slopes=alibi_slopes,
                             softcap=softcap, window=window, stream=stream)
@@ -190,6 +233,9 @@ def attn_fwd_mod(q, k, v, o=None, *, causal=False, scale=None, alibi_slopes=None
                  window=None, stream=None):
     """attn_fwd with the SoftCap modifier (``softcap``: None or cap > 0) and the
     causal sliding window (``window``: None or W >= 1 keys per row)."""
+    r = (_BINDING or _load_binding()).attn_fwd(q, k, v, o, causal, scale, alibi_slopes, softcap, window, stream)
+    if r is not None:
+        return _result(r)
     o = _fwd_args(q, k, v, o, alibi_slopes)
     B, Hq, Lq, D = q.shape
     Hkv, Lk = k.shape[1], k.shape[2]
@@ -235,6 +281,9 @@ def attn_decode(q, k, v, o=None, *, scale=None, alibi_slopes=None, softcap=None,
     ``num_splits`` = 0 lets the library choose.  ``workspace`` (uint8 GPU
     tensor) is allocated when not given.  Returns ``o`` [B, Hq, 1, D].
     """
+    r = (_BINDING or _load_binding()).attn_decode(q, k, v, o, scale, alibi_slopes, softcap, num_splits, workspace, stream)
+    if r is not None:
+        return _result(r)
     if softcap:
         return attn_decode_mod(q, k, v, o, scale=scale, alibi_slopes=alibi_slopes, softcap=softcap,
                                num_splits=num_splits, workspace=workspace, stream=stream)
@@ -252,6 +301,9 @@ def attn_decode(q, k, v, o=None, *, scale=None, alibi_slopes=None, softcap=None,
 def attn_decode_mod(q, k, v, o=None, *, scale=None, alibi_slopes=None, softcap=None, num_splits=0,
                     workspace=None, stream=None):
     """attn_decode with the SoftCap score modifier (``softcap``: None or cap > 0)."""
+    r = (_BINDING or _load_binding()).attn_decode(q, k, v, o, scale, alibi_slopes, softcap, num_splits, workspace, stream)
+    if r is not None:
+        return _result(r)
     o, workspace = _decode_args(q, k, v, o, alibi_slopes, num_splits, workspace)
     B, Hq, _, D = q.shape
     Hkv, Lk = k.shape[1], k.shape[2]
@@ -271,6 +323,9 @@ def attn_decode_noalloc(q, k, v, o=None, *, scale=None, alibi_slopes=None, softc
     """attn_decode_mod with the workspace in the library's static device array
     (no allocation inside the library; ``o`` is allocated here if not given).
     Calls that overlap on one GPU race on that array."""
+    r = (_BINDING or _load_binding()).attn_decode_noalloc(q, k, v, o, scale, alibi_slopes, softcap, num_splits, stream)
+    if r is not None:
+        return _result(r)
     _check_tensors(q, k, v, alibi_slopes)
     B, Hq, Lq, D = q.shape
     _require(Lq == 1, "decode takes one query token (q.shape[2] == 1)")
@@ -367,6 +422,9 @@ def _norm_args(op, x, chunks, workspace):
 
 def norm_l2(x, out=None, *, chunks=0, workspace=None, stream=None):
     """Row L2 norms of x [N, M] (single pass, split over the row): out [N] float32."""
+    r = (_BINDING or _load_binding()).norm_l2(x, out, chunks, workspace, stream)
+    if r is not None:
+        return _result(r)
     N, M, workspace = _norm_args("l2", x, chunks, workspace)
     if out is None:
         out = torch.empty(N, dtype=torch.float32, device=x.device)
@@ -378,6 +436,9 @@ def norm_l2(x, out=None, *, chunks=0, workspace=None, stream=None):
 
 def rmsnorm_rowmax(x, y=None, rowmax=None, *, eps=1e-6, chunks=0, workspace=None, stream=None):
     """y = x / sqrt(mean(x^2) + eps) (x's dtype) and rowmax [N] = max of each row of y (float32)."""
+    r = (_BINDING or _load_binding()).rmsnorm_rowmax(x, y, rowmax, eps, chunks, workspace, stream)
+    if r is not None:
+        return _result(r)
     N, M, workspace = _norm_args("rms", x, chunks, workspace)
     if y is None:
         y = torch.empty_like(x)

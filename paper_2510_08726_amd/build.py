@@ -12,6 +12,9 @@ no source-level spelling.  So the prefill units run hipcc's own compile steps
 (as printed by `hipcc -###`) and set the attribute on every kernel in the
 device IR between the front end and the back end, which leaves the kernels
 256 - 104 = 152 VGPRs at D = 128 and 256 - 56 = 200 at D = 64.
+
+The CPython module behind the tensor functions (_binding.so, host code only)
+is built next to it against the installed PyTorch.
 """
 
 import os
@@ -19,6 +22,7 @@ import re
 import shlex
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -27,6 +31,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 OBJDIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libattn.so")
+BINDING = os.path.join(PKG, "_binding.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 LLVM_DIS = "/opt/rocm/llvm/bin/llvm-dis"
@@ -102,8 +107,31 @@ def compile_with_agprs(cmd, cwd, agprs):
     return 0, ""
 
 
+def compile_binding():
+    """Compile csrc/binding.cpp to an object.  Returns (returncode, output)."""
+    import torch
+    inc = os.path.join(os.path.dirname(torch.__file__), "include")
+    cmd = ["g++", "-O2", "-std=c++20", "-fPIC", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", "-I", inc,
+           "-I", os.path.join(inc, "torch", "csrc", "api", "include"), "-I", "/opt/rocm/include",
+           "-I", sysconfig.get_paths()["include"], "-c", os.path.join(CSRC, "binding.cpp"),
+           "-o", os.path.join(OBJDIR, "binding.o")]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    return r.returncode, r.stdout
+
+
+def link(cmd, out):
+    """Run the link command `cmd` and move its result into place."""
+    tmp = out + ".tmp"
+    r = subprocess.run([*cmd, "-o", tmp], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("link failed:\n" + r.stdout)
+    os.replace(tmp, out)
+
+
 def build(verbose=False):
-    """Compile every source (in parallel) and link libattn.so.  Raises on failure."""
+    """Compile every source (in parallel) and link libattn.so and _binding.so.
+    Raises on failure."""
     os.makedirs(OBJDIR, exist_ok=True)
     jobs = []
     objs = []
@@ -126,20 +154,23 @@ def build(verbose=False):
         return p.returncode, p.stdout
 
     failed = []
-    with ThreadPoolExecutor(max_workers=len(jobs)) as ex:
+    with ThreadPoolExecutor(max_workers=len(jobs) + 1) as ex:
+        binding = ex.submit(compile_binding)
         for (name, _, _), (rc, out) in zip(jobs, ex.map(run, jobs)):
             if rc != 0:
                 failed.append(f"--- {name} ---\n{out}")
             elif verbose and out.strip():
                 print(out)
+        rc, out = binding.result()
+        if rc != 0:
+            failed.append(f"--- binding ---\n{out}")
     if failed:
-        raise RuntimeError("hipcc failed:\n" + "\n".join(failed))
-    tmp = LIB + ".tmp"
-    cmd = [HIPCC, "-shared", "-fPIC", f"--offload-arch={ARCH}", *objs, "-o", tmp]
-    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    if r.returncode != 0:
-        raise RuntimeError("link failed:\n" + r.stdout)
-    os.replace(tmp, LIB)
+        raise RuntimeError("compile failed:\n" + "\n".join(failed))
+    link([HIPCC, "-shared", "-fPIC", f"--offload-arch={ARCH}", *objs], LIB)
+    import torch
+    link(["g++", "-shared", os.path.join(OBJDIR, "binding.o"), "-L", PKG, "-lattn",
+          "-L", os.path.join(os.path.dirname(torch.__file__), "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu",
+          "-ltorch_python", "-Wl,-rpath,$ORIGIN"], BINDING)
     return LIB
 
 

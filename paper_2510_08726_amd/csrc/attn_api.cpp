@@ -2,6 +2,7 @@
 // dispatch to the gfx950 kernels, error reporting.  Every check runs before
 // any HIP call, so a rejected call enqueues nothing.
 
+#include <atomic>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -43,14 +44,18 @@ int hip_fail(hipError_t e) {
   return ATTN_ERR_HIP;
 }
 
-// Compute units of the current device (the grouped decode kernel wants one
-// workgroup per compute unit: each holds 128 KB of LDS, so more would run one
-// after another, each paying its start-up and merge again).
+// Compute units of the current device, 256 without one (the grouped decode
+// kernel wants one workgroup per compute unit: each holds 128 KB of LDS, so
+// more would run one after another, each paying its start-up and merge again).
+// Looked up once per device: it is asked for on every call that chooses its
+// own split.
 int compute_units() {
+  static std::atomic<int> cached[64];
   int dev = 0, n = 0;
-  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      n <= 0)
-    n = 256;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0) return 256;
+  if (dev < 64 && (n = cached[dev].load(std::memory_order_relaxed)) > 0) return n;
+  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return 256;
+  if (dev < 64) cached[dev].store(n, std::memory_order_relaxed);
   return n;
 }
 

@@ -1,0 +1,129 @@
+"""The C++ marshalling of the tensor functions against their Python checks:
+the same outputs for what both take (given or allocated outputs and
+workspaces, every option), the same errors for what they refuse, the current
+stream, and calls from several threads."""
+
+import threading
+
+import pytest
+import torch
+
+import paper_2510_08726_amd as pa
+from paper_2510_08726_amd.workloads import alibi_slopes, random_tensors
+
+pytestmark = pytest.mark.gpu
+
+
+def _qkv(B=2, Hq=4, Hkv=2, Lq=70, Lk=90, D=64, dt="f16"):
+    return [t.cuda() for t in random_tensors([(B, Hq, Lq, D), (B, Hkv, Lk, D), (B, Hkv, Lk, D)], dt, seed=5)]
+
+
+def _in_python(monkeypatch, f):
+    """f() with every call going through the Python checks and ctypes."""
+    with monkeypatch.context() as m:
+        m.setattr(pa, "_BINDING", pa._NotBuilt)
+        return f()
+
+
+FWD = [dict(), dict(causal=True), dict(causal=True, scale=0.3), dict(scale=1), dict(causal=True, softcap=5.0),
+       dict(causal=True, softcap=5, window=20), dict(causal=True, softcap=0, window=0), dict(causal=1, window=True)]
+
+
+@pytest.mark.parametrize("kw", FWD, ids=str)
+@pytest.mark.parametrize("alibi", [False, True])
+def test_prefill(monkeypatch, kw, alibi):
+    q, k, v = _qkv()
+    if alibi and kw.get("softcap"):
+        alibi = False
+    kw = dict(kw, alibi_slopes=alibi_slopes(4).cuda() if alibi else None)
+    for fn in (pa.attn_fwd, pa.attn_fwd_mod):
+        o = torch.full_like(q, float("nan"))
+        a, b = fn(q, k, v, **kw), fn(q, k, v, o, **kw)
+        c = _in_python(monkeypatch, lambda: fn(q, k, v, **kw))
+        assert b is o and torch.equal(a, c) and torch.equal(b, c) and a.dtype == q.dtype
+
+
+def test_decode_and_norms(monkeypatch):
+    q, k, v = _qkv(Lq=1, Lk=700, D=128, dt="bf16")
+    ws = torch.empty(1 << 16, dtype=torch.float32, device="cuda")
+    for kw in (dict(), dict(num_splits=3), dict(scale=0.2, softcap=4.0), dict(alibi_slopes=alibi_slopes(4).cuda()),
+               dict(workspace=ws)):
+        for fn in (pa.attn_decode, pa.attn_decode_mod, pa.attn_decode_noalloc):
+            if fn is pa.attn_decode_noalloc and "workspace" in kw:
+                continue
+            o = torch.full_like(q, float("nan"))
+            a, b = fn(q, k, v, **kw), fn(q, k, v, o, **kw)
+            c = _in_python(monkeypatch, lambda: fn(q, k, v, **kw))
+            assert b is o and torch.equal(a, c) and torch.equal(b, c)
+    for dt in (torch.float16, torch.bfloat16, torch.float32):
+        x = torch.randn(40, 9000, device="cuda").to(dt)
+        for kw in (dict(), dict(chunks=3), dict(workspace=ws)):
+            out, y, m = torch.empty(40, device="cuda"), torch.empty_like(x), torch.empty(40, device="cuda")
+            assert pa.norm_l2(x, out, **kw) is out
+            yy, mm = pa.rmsnorm_rowmax(x, y, m, eps=1e-5, **kw)
+            assert yy is y and mm is m
+            y2, m2 = pa.rmsnorm_rowmax(x, eps=1e-5, **kw)
+            y3, m3 = _in_python(monkeypatch, lambda: pa.rmsnorm_rowmax(x, eps=1e-5, **kw))
+            n3 = _in_python(monkeypatch, lambda: pa.norm_l2(x, **kw))
+            assert torch.equal(out, n3) and torch.equal(pa.norm_l2(x, **kw), n3)
+            assert torch.equal(y, y3) and torch.equal(y2, y3) and torch.equal(m, m3) and torch.equal(m2, m3)
+
+
+def test_what_is_refused_stays_refused(monkeypatch):
+    q, k, v = _qkv()
+    qd, x = q[:, :, :1].contiguous(), torch.randn(8, 64, device="cuda")
+    bad = [
+        lambda: pa.attn_fwd(q.cpu(), k, v), lambda: pa.attn_fwd(q.float(), k, v), lambda: pa.attn_fwd(q, k[:, :, :9], v),
+        lambda: pa.attn_fwd(q.transpose(1, 2), k, v), lambda: pa.attn_fwd(q[0], k, v), lambda: pa.attn_fwd(q[:1], k, v),
+        lambda: pa.attn_fwd(q, k.bfloat16(), v.bfloat16()), lambda: pa.attn_fwd(q, k, v, q[:, :, :5].contiguous()),
+        lambda: pa.attn_fwd(q, k, v, scale=float("nan")), lambda: pa.attn_fwd(q, k, v, scale="a"),
+        lambda: pa.attn_fwd(q, k, v, softcap=3.0), lambda: pa.attn_fwd(q, k, v, causal=True, softcap=-3.0),
+        lambda: pa.attn_fwd(q, k, v, causal=True, window=-1), lambda: pa.attn_fwd(q, k, v, window=5),
+        lambda: pa.attn_fwd(q, k, v, alibi_slopes=alibi_slopes(4)), lambda: pa.attn_fwd(q, k, v, alibi_slopes=alibi_slopes(3).cuda()),
+        lambda: pa.attn_fwd(q[:, :, :0], k, v), lambda: pa.attn_fwd(q[..., :32].contiguous(), k[..., :32].contiguous(), v[..., :32].contiguous()),
+        lambda: pa.attn_decode(q, k, v), lambda: pa.attn_decode(qd, k, v, num_splits=-1),
+        lambda: pa.attn_decode(qd, k, v, num_splits=None), lambda: pa.attn_decode_noalloc(q, k, v),
+        lambda: pa.attn_decode(qd, k, v, workspace=torch.empty(16, dtype=torch.uint8, device="cuda")),
+        lambda: pa.attn_decode_noalloc(qd, k, v, num_splits=100000),
+        lambda: pa.norm_l2(x.double()), lambda: pa.norm_l2(x[0]), lambda: pa.norm_l2(x.t()), lambda: pa.norm_l2(x.cpu()),
+        lambda: pa.norm_l2(x[:, :62].contiguous()), lambda: pa.norm_l2(x, chunks=None), lambda: pa.norm_l2(x, chunks=-2),
+        lambda: pa.norm_l2(x, torch.empty(7, device="cuda")), lambda: pa.rmsnorm_rowmax(x, x.half()),
+        lambda: pa.rmsnorm_rowmax(x, eps=-1.0), lambda: pa.rmsnorm_rowmax(x, eps=None),
+    ]
+    for i, f in enumerate(bad):
+        with pytest.raises(Exception) as here:
+            f()
+        with pytest.raises(Exception) as there:
+            _in_python(monkeypatch, f)
+        assert type(here.value) is type(there.value) and str(here.value) == str(there.value), (i, here.value, there.value)
+
+
+def test_current_stream_and_threads():
+    q, k, v = _qkv(Lq=300, Lk=300)
+    ref = pa.attn_fwd(q, k, v, causal=True)
+    torch.cuda.synchronize()
+    got = [None] * 4
+
+    def work(i):
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            for _ in range(20):
+                got[i] = pa.attn_fwd(q, k, v, causal=True)
+        s.synchronize()
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert all(torch.equal(g, ref) for g in got)
+    s = torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    x = torch.randn(8, 4096, device="cuda")
+    with torch.cuda.graph(g, stream=s):       # the call lands on the capturing stream
+        y, m = pa.rmsnorm_rowmax(x)
+    x.normal_()
+    g.replay()
+    torch.cuda.synchronize()
+    y2, m2 = pa.rmsnorm_rowmax(x)
+    assert torch.equal(y, y2) and torch.equal(m, m2)
