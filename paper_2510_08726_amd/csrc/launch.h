@@ -26,6 +26,7 @@ struct PrefillParams {
   int nitems;           // nqb * nheads, set by the launcher
   int nxcd;             // XCDs the workgroups are spread over, set by the launcher
   int hg;               // query heads per workgroup (sharing one KV head), set by the launcher
+  int sorted;           // 1: an XCD's items go out heaviest first, set by the launcher
 };
 
 struct DecodeParams {

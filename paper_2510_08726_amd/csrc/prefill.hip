@@ -752,7 +752,7 @@ __global__ __launch_bounds__(kThreads, kWgPerCu) __attribute__((amdgpu_num_vgpr(
   // row block w / hg of the query block.  Workgroup g runs on XCD g mod kXcds (the order in
   // which the dispatcher hands out the first workgroups), and each XCD takes
   // one contiguous share of the items, so the concurrent readers of a K/V
-  // tile share that XCD's L2.  Within an XCD, round r gives item r * Pl + c
+  // tile share that XCD's L2.  Within an XCD, unless p.sorted, round r gives item r * Pl + c
   // to the c-th of its Pl workgroups on even rounds and r * Pl + Pl - 1 - c on
   // odd ones: heavy and light query blocks pair up, and with causal masking
   // (key counts falling linearly with the block index) every workgroup gets
@@ -780,13 +780,54 @@ __global__ __launch_bounds__(kThreads, kWgPerCu) __attribute__((amdgpu_num_vgpr(
   };
   const int W = WIN ? p.window : 0;   // sliding window (keys per row)
   auto item_at = [&](int round, Item& it) __attribute__((always_inline)) {
-    const int sl = round * Pl + ((round & 1) ? Pl - 1 - c : c);
-    if (sl >= s1 - s0) return false;
-    const int s = s0 + sl;
-    it.kvh = s / per_kv;
-    const int rem = s - it.kvh * per_kv;
-    it.qb = p.nqb - 1 - rem / ngrp;
-    it.head = it.kvh * p.group + (rem % ngrp) * hg + wave % hg;
+    if (CAUSAL && p.sorted) {
+      // Heaviest first: the XCD's share is a contiguous range of the units
+      // (KV head, head group), nqb items each, from the heaviest (rank 0, the
+      // last query block) down; its ends may cut a unit.  Position pos of the
+      // share's items by rank is one of the nf whole units', of the unit cut
+      // at the start (ranks from r0 on) or of the one cut at the end (ranks
+      // below r1).  Workgroups c and c + Pl / 2 share a compute unit
+      // (measured): the first half takes the Pl / 2 heaviest items from the
+      // front and the second half the next ones from the back, so that a
+      // compute unit's two add up alike, and later rounds go to the
+      // workgroups back and forth.
+      // (Opaque copies of the share's ends keep what follows from them from
+      // being hoisted into registers held through the key loop.)
+      int sa = s0, sb = s1;
+      asm volatile("" : "+s"(sa), "+s"(sb));
+      const int i = c < Pl / 2 ? c : Pl + Pl / 2 - 1 - c;
+      int pos = round * Pl + ((round & 1) ? Pl - 1 - i : i);
+      if (pos >= sb - sa) return false;
+      const int nqb = p.nqb;
+      const int u0 = sa / nqb, u1 = sb / nqb;
+      const int c0 = sa - u0 * nqb, r1 = sb - u1 * nqb;
+      const int r0 = c0 > 0 ? c0 : nqb, uf = u0 + (c0 > 0), nf = u1 - uf;
+      int rank, u;
+      if (nf < 0) {                       // the share lies inside one unit
+        rank = c0 + pos;
+        u = u0;
+      } else {
+        const int ra = min(r0, r1), rb = max(r0, r1);
+        const int n1 = ra * (nf + 1), n2 = (rb - ra) * (r1 > r0 ? nf + 2 : nf);
+        int per = nf + 1, base = 0;
+        if (pos >= n1 + n2) { pos -= n1 + n2; base = rb; }
+        else if (pos >= n1) { pos -= n1; base = ra; per = r1 > r0 ? nf + 2 : nf; }
+        const int kq = pos / per, j = pos - kq * per;
+        rank = base + kq;
+        u = j < nf ? uf + j : (j == nf && rank < r1) ? u1 : u0;
+      }
+      it.qb = nqb - 1 - rank;
+      it.kvh = u / ngrp;
+      it.head = it.kvh * p.group + (u - it.kvh * ngrp) * hg + wave % hg;
+    } else {
+      const int sl = round * Pl + ((round & 1) ? Pl - 1 - c : c);
+      if (sl >= s1 - s0) return false;
+      const int s = s0 + sl;
+      it.kvh = s / per_kv;
+      const int rem = s - it.kvh * per_kv;
+      it.qb = p.nqb - 1 - rem / ngrp;
+      it.head = it.kvh * p.group + (rem % ngrp) * hg + wave % hg;
+    }
     it.hq = it.head % p.Hq;
     const int i0 = it.qb * bm;
     it.iw = i0 + BMW * (wave / hg);
@@ -1167,8 +1208,26 @@ hipError_t launch_t(const PrefillParams& p, hipStream_t stream) {
   q.nheads = p.B * p.Hq;
   q.nitems = q.nqb * (q.nheads / q.hg);
   if (q.nitems == 0) return hipSuccess;
-  const int grid = std::min(q.nitems, kWgPerCu * compute_units());
+  const int slots = kWgPerCu * compute_units();
+  int grid = std::min(q.nitems, slots);
   q.nxcd = grid % kXcds == 0 ? kXcds : 1;
+  // Causal items differ in length.  The KV-head-major deal balances them only
+  // over whole pairs of rounds: 3 x 12 heads of 3086 tokens (D 64, 900 items on
+  // 512 workgroups) took 92 us, 65 dealt heaviest first; 4 x 32/8 x 1614 110
+  // and 95, 6 x 32 x 1720 218 and 195.  But heaviest first spreads the readers
+  // of one K/V head over the rounds: where an XCD's K and V (its share of the
+  // heads) are far larger than its 4 MB L2 and the rounds are many, the
+  // imbalance is small and the refetching costs more (7 x 32 x 2544, 37 MB an
+  // XCD, 9 rounds: 433 us and 465, with 0.75 and 2.3 GB read).  Nor is there
+  // anything to balance where a window far shorter than the keys makes the
+  // items alike (16 heads x 5183, window 393: 42.9 and 43.9).
+  const int64_t kv_xcd = (int64_t)p.B * p.Hkv * p.Lk * D * 2 * (int64_t)sizeof(T) / kXcds;
+  q.sorted = CAUSAL && slots % (2 * kXcds) == 0 && q.nitems % (2 * slots) != 0 &&
+             (q.nitems < 6 * slots || kv_xcd <= (int64_t)12 << 20) && (!WIN || 4 * (int64_t)p.window >= p.Lk);
+  if (q.sorted) {
+    grid = slots;
+    q.nxcd = kXcds;
+  }
   hipLaunchKernelGGL((prefill_kernel<D, T, CAUSAL, ALIBI, CAP, WIN>), dim3(grid), dim3(kThreads), 0, stream, q);
   return hipGetLastError();
 }
