@@ -121,6 +121,34 @@ int attn_fwd_mod(const void* Q, const void* K, const void* V, void* O,
                  attn_dtype dtype, hipStream_t stream);
 
 /*
+ * attn_fwd_mod with a workspace for calls with few query rows (split-k update,
+ * Section "Split-K Update", applied to a block of queries): where the rows
+ * alone cannot fill the compute units, the keys are divided over workgroups
+ * whose fp32 partials a second kernel combines.
+ *
+ *   attn_fwd_num_splits       key ranges that a call of these sizes is divided
+ *                             into when it has a workspace: 1 for most calls
+ *                             (no workspace is used), 0 for invalid sizes.
+ *                             Depends on the current device's compute units
+ *                             (256 if it cannot be queried).
+ *   attn_fwd_workspace_bytes  workspace of (B, Hq, Lq, D, num_splits): 0 for
+ *                             num_splits = 1 and for invalid sizes.
+ *   attn_fwd_split            workspace: NULL (then exactly attn_fwd_mod), or a
+ *                             device buffer, 16-byte aligned, of at least
+ *                             attn_fwd_workspace_bytes(B, Hq, Lq, D,
+ *                             attn_fwd_num_splits(...)) bytes, used until the
+ *                             call's kernels end on `stream`.
+ * Errors of attn_fwd_split: as attn_fwd_mod, and ATTN_ERR_WORKSPACE for a
+ * workspace that is too small or not aligned.
+ */
+int attn_fwd_num_splits(int B, int Hq, int Hkv, int Lq, int Lk, int D, int causal, int window);
+size_t attn_fwd_workspace_bytes(int B, int Hq, int Lq, int D, int num_splits);
+int attn_fwd_split(const void* Q, const void* K, const void* V, void* O,
+                   int B, int Hq, int Hkv, int Lq, int Lk, int D,
+                   int causal, float scale, const float* alibi_slopes, float softcap, int window,
+                   void* workspace, size_t workspace_bytes, attn_dtype dtype, hipStream_t stream);
+
+/*
  * Bytes of decode workspace needed for (B, Hq, D, num_splits), num_splits >= 1
  * (resolve 0 with attn_decode_num_splits first).  Returns 0 for invalid sizes.
  *
@@ -218,6 +246,8 @@ int attn_decode_noalloc(const void* Q, const void* K, const void* V, void* O,
  * for these arguments, written to buf as a NUL-terminated string such as
  * "prefill_kernel<128,f16,1,0,0,0>" (head dim, element type, then the
  * causal, ALiBi, SoftCap and window template flags).  Host only: no HIP call.
+ * (A call whose query rows cannot give every compute unit a workgroup of that
+ * kernel may run prefill_split_kernel<D,type,G,alibi,softcap> instead.)
  * For coverage checks and profiles of the rolling-update kernel (Section
  * "Rolling Update").  alibi: non-zero if slopes would be passed.
  * Errors: the argument errors of attn_fwd_mod; ATTN_ERR_SHAPE if buf is NULL

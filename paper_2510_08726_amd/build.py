@@ -52,6 +52,7 @@ DEVICE = ["-x", "hip", f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "
 UNITS = [(f"prefill{k}", "prefill.hip", ["-fno-honor-nans", f"-DATTN_PREFILL_SHARD={k}", "-save-temps"])
          for k in range(4)] + [("decode", "decode.hip", ["-save-temps"]), ("peaks", "peaks.hip", ["-save-temps"]),
             ("norms", "norms.hip", ["-save-temps"]),
+            ("prefill_split", "prefill_split.hip", ["-fno-honor-nans", "-save-temps"]),
             ("attn_api", "attn_api.cpp", [])]
 
 
@@ -148,7 +149,7 @@ def build(verbose=False):
 
     def run(job):
         name, src, cmd = job
-        if src == "prefill.hip":
+        if name[len("prefill"):].isdigit():
             return compile_with_agprs(cmd, unit_dir(name), PREFILL_AGPRS[int(name[len("prefill"):])])
         p = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, cwd=unit_dir(name))
         return p.returncode, p.stdout

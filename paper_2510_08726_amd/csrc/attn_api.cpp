@@ -92,10 +92,23 @@ const char* attn_status_string(int status) {
 
 int attn_last_hip_error(void) { return g_last_hip_error; }
 
-int attn_fwd_mod(const void* Q, const void* K, const void* V, void* O,
-                 int B, int Hq, int Hkv, int Lq, int Lk, int D,
-                 int causal, float scale, const float* alibi_slopes, float softcap, int window,
-                 attn_dtype dtype, hipStream_t stream) {
+int attn_fwd_num_splits(int B, int Hq, int Hkv, int Lq, int Lk, int D, int causal, int window) {
+  if (!shape_ok(B, Hq, Hkv, Lq, Lk) || (D != 64 && D != 128) || window < 0) return 0;
+  return attn::prefill_split_plan(B, Hq, Hkv, Lq, Lk, D, causal != 0, window, compute_units(),
+                                  attn::kMaxPrefillSplits).splits;
+}
+
+size_t attn_fwd_workspace_bytes(int B, int Hq, int Lq, int D, int num_splits) {
+  if (B < 1 || Hq < 1 || Lq < 1 || num_splits < 1 || (D != 64 && D != 128)) return 0;
+  if (num_splits == 1) return 0;
+  const size_t bytes = (size_t)B * Hq * Lq * num_splits * (size_t)(D + 2) * sizeof(float);
+  return (bytes + 255) & ~(size_t)255;
+}
+
+int attn_fwd_split(const void* Q, const void* K, const void* V, void* O,
+                   int B, int Hq, int Hkv, int Lq, int Lk, int D,
+                   int causal, float scale, const float* alibi_slopes, float softcap, int window,
+                   void* workspace, size_t workspace_bytes, attn_dtype dtype, hipStream_t stream) {
   if (!Q || !K || !V || !O) return ATTN_ERR_NULL;
   if (!shape_ok(B, Hq, Hkv, Lq, Lk) || !std::isfinite(scale)) return ATTN_ERR_SHAPE;
   if (!std::isfinite(softcap) || softcap < 0.f || window < 0) return ATTN_ERR_SHAPE;
@@ -108,6 +121,11 @@ int attn_fwd_mod(const void* Q, const void* K, const void* V, void* O,
   const int bm = attn::prefill_block_rows();
   const int64_t nqb = ((int64_t)Lq + bm - 1) / bm;
   if (nqb * B * Hq > kMaxGrid) return ATTN_ERR_SHAPE;
+  const attn::PrefillSplitPlan plan = attn::prefill_split_plan(B, Hq, Hkv, Lq, Lk, D, causal != 0, window, compute_units(),
+                                                               workspace ? attn::kMaxPrefillSplits : 1);
+  const int S = plan.splits;
+  if (S > 1 && (workspace_bytes < attn_fwd_workspace_bytes(B, Hq, Lq, D, S) || (reinterpret_cast<uintptr_t>(workspace) & 15)))
+    return ATTN_ERR_WORKSPACE;
 
   attn::PrefillParams p{};
   p.q = Q; p.k = K; p.v = V; p.o = O;
@@ -130,8 +148,19 @@ int attn_fwd_mod(const void* Q, const void* K, const void* V, void* O,
     p.qsign = std::signbit(scale) ? 0x80008000u : 0u;
   }
   p.nqb = (int)nqb;
+  p.kgroups = plan.kgroups;
+  p.splits = S;
+  p.ws = static_cast<float*>(workspace);
   hipError_t e = attn::launch_prefill(p, stream);
   return e == hipSuccess ? ATTN_OK : hip_fail(e);
+}
+
+int attn_fwd_mod(const void* Q, const void* K, const void* V, void* O,
+                 int B, int Hq, int Hkv, int Lq, int Lk, int D,
+                 int causal, float scale, const float* alibi_slopes, float softcap, int window,
+                 attn_dtype dtype, hipStream_t stream) {
+  return attn_fwd_split(Q, K, V, O, B, Hq, Hkv, Lq, Lk, D, causal, scale, alibi_slopes, softcap, window, nullptr, 0,
+                        dtype, stream);
 }
 
 int attn_fwd(const void* Q, const void* K, const void* V, void* O,

@@ -152,10 +152,20 @@ PyObject* py_attn_fwd(PyObject*, PyObject* const* x, Py_ssize_t n) {
   if (!attn_args(x[0], x[1], x[2], x[3], x[5], x[6], a)) return none();
   const void *q = a.q->data_ptr(), *k = a.k->data_ptr(), *v = a.v->data_ptr();
   void* o = a.o.data_ptr();
+  // Few rows against many keys: a workspace, which lives on this stream like
+  // the call itself.
+  at::Tensor ws;
+  size_t bytes = 0;
+  const int S = attn_fwd_num_splits(a.B, a.Hq, a.Hkv, a.Lq, a.Lk, a.D, causal, window);
+  if (S > 1) {
+    bytes = attn_fwd_workspace_bytes(a.B, a.Hq, a.Lq, a.D, S);
+    ws = at::empty({(int64_t)bytes}, a.q->options().dtype(at::kByte));
+  }
+  void* w = S > 1 ? ws.data_ptr() : nullptr;
   const hipStream_t s = stream();
   const int rc = unlocked([&] {
-    return attn_fwd_mod(q, k, v, o, a.B, a.Hq, a.Hkv, a.Lq, a.Lk, a.D, causal, a.scale, a.slopes, cap, window,
-                        a.dtype, s);
+    return attn_fwd_split(q, k, v, o, a.B, a.Hq, a.Hkv, a.Lq, a.Lk, a.D, causal, a.scale, a.slopes, cap, window, w,
+                          bytes, a.dtype, s);
   });
   return result(rc, x[3], std::move(a.o));
   END_HANDLE_TH_ERRORS

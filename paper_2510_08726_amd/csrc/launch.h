@@ -26,6 +26,9 @@ struct PrefillParams {
   int nitems;           // nqb * nheads, set by the launcher
   int nxcd;             // XCDs the workgroups are spread over, set by the launcher
   int hg;               // query heads per workgroup (sharing one KV head), set by the launcher
+  int kgroups;          // key groups of prefill_split.hip (2 or 4), 0 for prefill.hip
+  int splits;           // its key ranges (1: none)
+  float* ws;            // its partials, for splits > 1: [splits, B*Hq*Lq, D], then (max, sum) [splits, B*Hq*Lq, 2]
   int sorted;           // 1: an XCD's items go out heaviest first, set by the launcher
 };
 
@@ -71,6 +74,17 @@ inline int decode_split_heads(int group) {
 
 int prefill_block_rows();
 hipError_t launch_prefill(const PrefillParams& p, hipStream_t stream);
+// Few query rows: keys split inside the workgroup, and with a workspace over
+// workgroups (prefill_split.hip); launch_prefill takes it when the plan of the
+// call says so.
+constexpr int kMaxPrefillSplits = 32;
+struct PrefillSplitPlan {
+  int kgroups;          // key groups of its workgroups (2 or 4), or 0: prefill.hip runs
+  int splits;           // key ranges over workgroups that it wants (needs a workspace when > 1)
+};
+PrefillSplitPlan prefill_split_plan(int B, int Hq, int Hkv, int Lq, int Lk, int D, bool causal, int window, int cus,
+                                    int max_splits);
+hipError_t launch_prefill_split(const PrefillParams& p, hipStream_t stream);
 // One per (head dim, element type); launch_prefill dispatches to them.
 hipError_t launch_prefill_d128_f16(const PrefillParams& p, hipStream_t stream);
 hipError_t launch_prefill_d128_bf16(const PrefillParams& p, hipStream_t stream);

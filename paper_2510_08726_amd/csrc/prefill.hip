@@ -1261,6 +1261,7 @@ hipError_t launch_prefill_d64_bf16(const PrefillParams& p, hipStream_t s) { retu
 int prefill_block_rows() { return BM; }
 
 hipError_t launch_prefill(const PrefillParams& p, hipStream_t stream) {
+  if (p.kgroups > 0) return launch_prefill_split(p, stream);
   if (p.D == 64) return p.bf16 ? launch_prefill_d64_bf16(p, stream) : launch_prefill_d64_f16(p, stream);
   return p.bf16 ? launch_prefill_d128_bf16(p, stream) : launch_prefill_d128_f16(p, stream);
 }

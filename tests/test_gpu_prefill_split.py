@@ -1,0 +1,125 @@
+"""Prompts with few query rows (keys split inside the workgroup, and with a
+workspace over workgroups), at the sizes where that can go wrong: one row,
+row blocks of 32 and pairs of them, groups of one, an odd and an even number of
+heads, key groups and key ranges without keys, rows without keys; and the wide
+kernel at small ragged sizes, with enough heads that it runs."""
+
+import ctypes
+
+import pytest
+import torch
+
+import paper_2510_08726_amd as pa
+from paper_2510_08726_amd.workloads import alibi_slopes, random_tensors
+from gpu_common import assert_close, host32, oracle_fwd, run_fwd
+from kernel_cases import PREFILL_VARIANT_CASES, case_id
+
+pytestmark = pytest.mark.gpu
+
+# B, Hq, Hkv, Lq, Lk, D, dtype, causal, alibi, softcap, window
+# (Both numbers of key groups, one and several key ranges.)
+CASES = [
+    (1, 4, 2, 1, 1, 128, "f16", True, False, None, None),
+    (1, 4, 4, 33, 31, 64, "bf16", True, False, None, None),       # rows without keys, odd block pair
+    (2, 6, 2, 32, 129, 128, "bf16", True, False, None, None),     # 3 heads per KV head: row pairs
+    (1, 4, 1, 65, 200, 64, "f16", False, False, None, None),
+    (1, 2, 2, 64, 2500, 128, "f16", True, False, None, None),     # key ranges over workgroups
+    (1, 8, 2, 31, 4100, 64, "bf16", True, True, None, None),
+    (1, 4, 2, 40, 3001, 128, "f16", True, False, 4.0, None),
+    (1, 4, 4, 70, 3000, 64, "f16", True, False, None, 1500),
+    (1, 4, 2, 70, 3000, 128, "bf16", True, False, 5.0, 2047),
+    (1, 4, 2, 70, 3031, 128, "f16", True, True, None, 2000),
+    (1, 2, 1, 100, 5000, 128, "bf16", False, True, None, None),
+    (2, 4, 2, 2100, 40, 64, "f16", True, False, None, None),      # most rows without keys
+    (1, 16, 8, 700, 900, 64, "bf16", False, False, None, None),
+    (2, 12, 3, 33, 2600, 128, "f16", True, False, None, None),    # 4 heads per KV head
+]
+
+
+def _inputs(case):
+    B, Hq, Hkv, Lq, Lk, D, dt, causal, alibi, cap, win = case
+    q, k, v = random_tensors([(B, Hq, Lq, D), (B, Hkv, Lk, D), (B, Hkv, Lk, D)], dt, seed=Lq + Lk)
+    if cap:
+        q = (q.float() * 4).to(q.dtype)
+    return q, k, v, alibi_slopes(Hq) if alibi else None
+
+
+def _ranges(case):
+    B, Hq, Hkv, Lq, Lk, D, dt, causal, alibi, cap, win = case
+    return pa.load_library().attn_fwd_num_splits(B, Hq, Hkv, Lq, Lk, D, int(causal), win or 0)
+
+
+def test_some_cases_use_key_ranges():
+    assert sum(_ranges(c) > 1 for c in CASES) >= 5 and sum(_ranges(c) == 1 for c in CASES) >= 4
+
+
+@pytest.mark.parametrize("case", CASES, ids=case_id)
+def test_few_rows_match_the_oracle(case):
+    B, Hq, Hkv, Lq, Lk, D, dt, causal, alibi, cap, win = case
+    print(f"prefill split case {case}, {_ranges(case)} key ranges", flush=True)
+    q, k, v, sl = _inputs(case)
+    kw = dict(scale=D ** -0.5, causal=causal, slopes=sl, softcap=cap, window=win)
+    ref = oracle_fwd(q, k, v, **kw)
+    o = run_fwd(q, k, v, **kw)
+    assert_close(host32(o), ref, f"prefill split {case}")
+    assert torch.equal(o, run_fwd(q, k, v, **kw))                 # the same bits again
+    # Without a workspace the keys stay in one range.
+    dev, vp = torch.device("cuda"), ctypes.c_void_p
+    qd, kd, vd = q.to(dev), k.to(dev), v.to(dev)
+    sd = None if sl is None else sl.to(dev)
+    o1 = torch.full_like(qd, float("nan"))
+    rc = pa.load_library().attn_fwd_mod(vp(qd.data_ptr()), vp(kd.data_ptr()), vp(vd.data_ptr()), vp(o1.data_ptr()), B, Hq,
+                                        Hkv, Lq, Lk, D, int(causal), D ** -0.5, None if sd is None else vp(sd.data_ptr()),
+                                        float(cap or 0), win or 0, 0 if dt == "f16" else 1,
+                                        vp(torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    assert rc == 0
+    assert_close(host32(o1), ref, f"prefill split {case}, one range")
+
+
+def test_negative_and_zero_scale_and_constant_values():
+    q, k, v, _ = _inputs((1, 4, 2, 50, 3000, 128, "f16", True, False, None, None))
+    for scale in (-0.05, 0.0):
+        ref = oracle_fwd(q, k, v, scale=scale, causal=True)
+        assert_close(host32(run_fwd(q, k, v, scale=scale, causal=True)), ref, f"scale {scale}")
+    one = torch.full_like(v, 1.5)
+    assert torch.all(run_fwd(q, k, one, scale=0.1, causal=True) == 1.5)
+
+
+@pytest.mark.parametrize("case", PREFILL_VARIANT_CASES, ids=case_id)
+def test_wide_kernel_at_small_ragged_sizes(case):
+    """The small cases of every prefill kernel, with the batch repeated until
+    the wide kernel runs; a few (batch, head) slices against the oracle, the
+    repeats bit for bit."""
+    B, Hq, Hkv, Lq, Lk, D, dt, causal, alibi, cap, win = case
+    R = 66
+    q, k, v, sl = _inputs(case)
+    dev = torch.device("cuda")
+    rep = [t.to(dev).repeat(R, 1, 1, 1) for t in (q, k, v)]
+    hg = next(h for h in (4, 2, 1) if (Hq // Hkv) % h == 0)
+    assert -(-Lq // (128 // hg)) * (R * Hq // hg) > 256          # past any threshold of the narrow path
+    o = pa.attn_fwd(*rep, causal=causal, scale=D ** -0.5, alibi_slopes=None if sl is None else sl.to(dev), softcap=cap,
+                    window=win)
+    torch.cuda.synchronize()
+    for b in range(1, R):
+        assert torch.equal(o[b], o[0]), b
+    ref = oracle_fwd(q, k, v, scale=D ** -0.5, causal=causal, slopes=sl, softcap=cap, window=win)
+    assert_close(host32(o[:1]), ref, f"wide kernel {case}")
+
+
+def test_capture_in_a_graph_with_key_ranges():
+    case = CASES[4]
+    q, k, v, _ = _inputs(case)
+    assert _ranges(case) > 1
+    q, k, v = q.cuda(), k.cuda(), v.cuda()
+    eager = pa.attn_fwd(q, k, v, causal=True)
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g):
+        o = pa.attn_fwd(q, k, v, causal=True)
+    for _ in range(3):
+        o.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(o, eager)
+        assert torch.equal(pa.attn_fwd(q, k, v, causal=True), eager)

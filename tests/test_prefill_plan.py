@@ -1,0 +1,48 @@
+"""Host logic of the split of prompts with few rows (no device here: 256
+compute units), and the checks of its workspace."""
+
+import ctypes
+
+import pytest
+
+import paper_2510_08726_amd as pa
+
+FAKE = ctypes.c_void_p(0x10000)
+
+
+@pytest.fixture(scope="module")
+def lib():
+    try:
+        lib = pa.load_library()
+    except RuntimeError:
+        import __graft_entry__
+        __graft_entry__.build()
+        lib = pa.load_library()
+    lib.attn_fwd_workspace_bytes.restype = ctypes.c_size_t
+    return lib
+
+
+def test_key_ranges(lib):
+    S = lib.attn_fwd_num_splits
+    assert S(4, 32, 32, 2048, 2048, 128, 1, 0) == 1        # enough rows
+    assert S(1, 32, 8, 64, 16000, 128, 1, 0) == 8          # 32 workgroups of 256
+    assert S(1, 32, 8, 500, 6100, 128, 1, 0) == 1          # 256 workgroups in one range
+    assert S(2, 32, 16, 130, 13392, 128, 1, 0) == 2
+    assert S(1, 32, 8, 64, 500, 128, 1, 0) == 1            # too few keys to pay for a second kernel
+    assert S(1, 32, 8, 64, 16000, 128, 1, 300) == 1        # nor in the window
+    assert S(0, 32, 8, 64, 16000, 128, 1, 0) == 0 and S(1, 32, 8, 64, 16000, 96, 1, 0) == 0
+    assert 1 <= S(1, 1, 1, 1, 8000000, 128, 0, 0) <= 32
+
+
+def test_workspace(lib):
+    W = lib.attn_fwd_workspace_bytes
+    assert W(1, 32, 64, 128, 1) == 0 and W(0, 32, 64, 128, 4) == 0 and W(1, 32, 64, 96, 4) == 0
+    assert W(1, 32, 64, 128, 8) == 32 * 64 * 8 * 130 * 4
+
+    def call(ws, nbytes):
+        return lib.attn_fwd_split(FAKE, FAKE, FAKE, FAKE, 1, 32, 8, 64, 16000, 128, 1, ctypes.c_float(0.1), None,
+                                  ctypes.c_float(0.0), 0, ws, ctypes.c_size_t(nbytes), 0, None)
+
+    need = W(1, 32, 64, 128, 8)
+    assert call(FAKE, need - 1) == pa.ATTN_ERR_WORKSPACE
+    assert call(ctypes.c_void_p(0x10008), need) == pa.ATTN_ERR_WORKSPACE
