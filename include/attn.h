@@ -165,12 +165,13 @@ size_t attn_decode_workspace_bytes(int B, int Hq, int D, int num_splits);
 
 /*
  * The number of key chunks attn_decode uses when num_splits == 0 (the library
- * heuristic): about one workgroup per compute unit of the current device (256
- * if it cannot be queried).  With one query head per KV head (or more than
- * 32), one workgroup per (chunk, KV head, batch, query-head group) and
- * chunks of at least 256 keys; with 2..32 query heads per KV head, served
- * together by one workgroup per (chunk, KV head, batch), chunks of at least
- * 128 keys.
+ * heuristic), from the compute units of the current device (256 if it cannot
+ * be queried).  With 2..32 query heads per KV head, served together by one
+ * workgroup per (chunk, KV head, batch): the most chunks whose workgroups do
+ * not outnumber the compute units, of at least 128 keys.  With one query head
+ * per KV head (or more than 32), one workgroup per (chunk, KV head, batch,
+ * query-head group): one workgroup per compute unit if that divides evenly,
+ * else up to two, chunks of at least 256 keys.
  * Returns a value >= 1, or 0 for invalid sizes.
  */
 int attn_decode_num_splits(int B, int Hq, int Hkv, int Lk, int D);

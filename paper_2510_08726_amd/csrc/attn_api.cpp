@@ -2,6 +2,7 @@
 // dispatch to the gfx950 kernels, error reporting.  Every check runs before
 // any HIP call, so a rejected call enqueues nothing.
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdint>
@@ -21,7 +22,6 @@ thread_local int g_last_hip_error = 0;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int64_t kMaxGrid = std::numeric_limits<int32_t>::max();
 constexpr int kMinChunk = 256;    // keys per decode chunk chosen by the heuristic (one head per KV head)
-constexpr int kBlocksPerCu = 1;   // per-head decode workgroups per compute unit chosen by the heuristic
 constexpr int kMinChunkGrouped = 128;   // grouped heads: at least one 32-key tile per wave
 
 bool shape_ok(int B, int Hq, int Hkv, int Lq, int Lk) {
@@ -63,6 +63,11 @@ int compute_units() {
 int decode_heads_per_block(int group) {
   const int gh = attn::decode_split_heads(group);
   return gh == 0 ? group : gh;
+}
+
+// At most one chunk per `least` keys, at least one chunk.
+int clamp_splits(int64_t s, int Lk, int least) {
+  return (int)std::max<int64_t>(std::min(s, ((int64_t)Lk + least - 1) / least), 1);
 }
 
 const char* dtype_name(attn_dtype dtype) { return dtype == ATTN_BF16 ? "bf16" : "f16"; }
@@ -172,28 +177,24 @@ int attn_fwd(const void* Q, const void* K, const void* V, void* O,
 
 int attn_decode_num_splits(int B, int Hq, int Hkv, int Lk, int D) {
   if (!shape_ok(B, Hq, Hkv, 1, Lk) || (D != 64 && D != 128)) return 0;
-  const int group = Hq / Hkv;
+  const int group = Hq / Hkv, cus = compute_units();
   if (group >= 2 && group <= 32) {
-    // The grouped kernel: one workgroup per (chunk, KV head, batch).
-    const int64_t units = (int64_t)B * Hkv;
-    int64_t s = (compute_units() + units - 1) / units;
-    const int64_t smax = ((int64_t)Lk + kMinChunkGrouped - 1) / kMinChunkGrouped;
-    if (s > smax) s = smax;
-    if (s < 1) s = 1;
-    return (int)s;
+    // The grouped kernel: one workgroup per (chunk, KV head, batch), and with
+    // its LDS one workgroup at a time per compute unit (D = 128), so the most
+    // chunks that still run in one round: 6 x 64/8 heads, 4050 keys took 41
+    // us in 6 chunks (288 workgroups), 29 in 5; 13 x 32/8, 20000 keys 230 in 3
+    // and 170 in 2; 11 x 32/16, 3000 keys 63 in 2 and 53 in 1.
+    return clamp_splits(cus / ((int64_t)B * Hkv), Lk, kMinChunkGrouped);
   }
-  // The per-head kernel: about one workgroup per compute unit (measured at
-  // steady clock with nontemporal K/V loads on five shapes, batch 1-32,
-  // 2048-32768 keys, D 64 and 128: 2-4 % ahead of two per compute unit on
-  // four of them, 1 % behind on the ALiBi one).
-  const int64_t groups = Hq / Hkv / decode_heads_per_block(Hq / Hkv);
-  const int64_t units = (int64_t)B * Hkv * groups;
-  const int64_t target = (int64_t)kBlocksPerCu * compute_units();
-  int64_t s = (target + units - 1) / units;
-  const int64_t smax = ((int64_t)Lk + kMinChunk - 1) / kMinChunk;
-  if (s > smax) s = smax;
-  if (s < 1) s = 1;
-  return (int)s;
+  // The per-head kernel: one workgroup per compute unit where the heads divide
+  // them evenly (measured at steady clock with nontemporal K/V loads, batch
+  // 1-32, 2048-32768 keys, D 64 and 128: 2-4 % ahead of two per compute unit
+  // on four of five shapes, 1 % behind on the fifth), else up to two, which
+  // leaves no compute unit a second chunk alone: 9 x 16 heads (D = 64), 8260
+  // keys took 69 us in 2 chunks and 51 in 3, 3 x 32, 2280 keys 25.6 in 3 and
+  // 23.7 in 5, 5 x 12 (D = 64), 9942 keys 32 in 5 and 28 in 8.
+  const int64_t units = (int64_t)B * Hkv * (group / decode_heads_per_block(group));
+  return clamp_splits(cus % units == 0 || units > cus ? (cus + units - 1) / units : 2 * cus / units, Lk, kMinChunk);
 }
 
 size_t attn_decode_workspace_bytes(int B, int Hq, int D, int num_splits) {
@@ -259,6 +260,13 @@ int attn_decode_mod(const void* Q, const void* K, const void* V, void* O,
   const int rc = decode_check(Q, K, V, O, B, Hq, Hkv, Lk, D, scale, softcap, num_splits, dtype, &S);
   if (rc != ATTN_OK) return rc;
   if (!workspace) return ATTN_ERR_NULL;
+  // A workspace kept for one chunk per compute unit still serves where the
+  // library would choose more.
+  if (num_splits == 0 && workspace_bytes < attn_decode_workspace_bytes(B, Hq, D, S)) {
+    const int group = Hq / Hkv;
+    const int64_t units = (int64_t)B * Hkv * (group / decode_heads_per_block(group));
+    S = std::min(S, clamp_splits((compute_units() + units - 1) / units, Lk, kMinChunk));
+  }
   const size_t need = attn_decode_workspace_bytes(B, Hq, D, S);
   if (workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 15)) return ATTN_ERR_WORKSPACE;
   return decode_launch(Q, K, V, O, B, Hq, Hkv, Lk, D, scale, alibi_slopes, softcap, S, workspace, dtype, stream);

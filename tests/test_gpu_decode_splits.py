@@ -1,0 +1,52 @@
+"""The library's chunk counts at the edges of their rule (workgroups just below
+and above the compute units), the combine of few, many and empty chunks, and a
+workspace kept from a smaller chunk count."""
+
+import pytest
+import torch
+
+import paper_2510_08726_amd as pa
+from paper_2510_08726_amd.workloads import random_tensors
+from gpu_common import assert_close, host32, oracle_fwd
+
+pytestmark = pytest.mark.gpu
+
+
+def _cus():
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+def test_grouped_chunks_fill_one_round():
+    cu = _cus()
+    for B in (1, 5, 6, 11, 16, 17):
+        S = pa.attn_decode_num_splits(B, 64, 16, 1 << 20, 128)
+        assert S == max(cu // (16 * B), 1) and (B * 16 > cu or B * 16 * S <= cu)
+
+
+# B, Hq, Hkv, Lk, D, dtype, num_splits
+CASES = [(6, 16, 8, 700, 128, "f16", 0), (11, 32, 16, 300, 64, "bf16", 0), (3, 12, 12, 3000, 64, "f16", 0),
+         (9, 16, 16, 1000, 128, "bf16", 0), (2, 8, 2, 500, 128, "f16", 7), (2, 4, 4, 500, 64, "f16", 33),
+         (1, 4, 2, 90, 128, "bf16", 90), (1, 4, 4, 40, 64, "bf16", 300), (1, 8, 2, 2000, 64, "f16", 65)]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
+def test_chunks_and_combine(case):
+    B, Hq, Hkv, Lk, D, dt, S = case
+    print(f"decode chunks {case}", flush=True)
+    q, k, v = random_tensors([(B, Hq, 1, D), (B, Hkv, Lk, D), (B, Hkv, Lk, D)], dt, seed=Lk)
+    o = pa.attn_decode(q.cuda(), k.cuda(), v.cuda(), scale=D ** -0.5, num_splits=S)
+    torch.cuda.synchronize()
+    assert_close(host32(o), oracle_fwd(q, k, v, scale=D ** -0.5, causal=True), f"decode {case}")
+
+
+def test_workspace_kept_from_a_smaller_chunk_count():
+    cu = _cus()
+    B, H, Lk, D = 3, 32, 4000, 64                                   # 96 heads: 5 chunks of 256 compute units, once 3
+    q, k, v = (t.cuda() for t in random_tensors([(B, H, 1, D), (B, H, Lk, D), (B, H, Lk, D)], "f16", seed=3))
+    S, kept = pa.attn_decode_num_splits(B, H, H, Lk, D), -(-cu // (B * H))
+    ref = pa.attn_decode(q, k, v, num_splits=kept)
+    ws = torch.empty(pa.attn_decode_workspace_bytes(B, H, D, kept), dtype=torch.uint8, device="cuda")
+    assert torch.equal(pa.attn_decode(q, k, v, workspace=ws), ref if S > kept else pa.attn_decode(q, k, v))
+    if kept > 1:
+        with pytest.raises(pa.AttnError):
+            pa.attn_decode(q, k, v, workspace=ws[:ws.numel() - 256])
