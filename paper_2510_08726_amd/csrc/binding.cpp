@@ -153,15 +153,19 @@ PyObject* py_attn_fwd(PyObject*, PyObject* const* x, Py_ssize_t n) {
   const void *q = a.q->data_ptr(), *k = a.k->data_ptr(), *v = a.v->data_ptr();
   void* o = a.o.data_ptr();
   // Few rows against many keys: a workspace, which lives on this stream like
-  // the call itself.
+  // the call itself.  Where memory has run out the call does without it.
   at::Tensor ws;
   size_t bytes = 0;
   const int S = attn_fwd_num_splits(a.B, a.Hq, a.Hkv, a.Lq, a.Lk, a.D, causal, window);
   if (S > 1) {
     bytes = attn_fwd_workspace_bytes(a.B, a.Hq, a.Lq, a.D, S);
-    ws = at::empty({(int64_t)bytes}, a.q->options().dtype(at::kByte));
+    try {
+      ws = at::empty({(int64_t)bytes}, a.q->options().dtype(at::kByte));
+    } catch (const c10::OutOfMemoryError&) {
+      bytes = 0;
+    }
   }
-  void* w = S > 1 ? ws.data_ptr() : nullptr;
+  void* w = bytes ? ws.data_ptr() : nullptr;
   const hipStream_t s = stream();
   const int rc = unlocked([&] {
     return attn_fwd_split(q, k, v, o, a.B, a.Hq, a.Hkv, a.Lq, a.Lk, a.D, causal, a.scale, a.slopes, cap, window, w,

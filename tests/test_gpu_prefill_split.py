@@ -123,3 +123,20 @@ def test_capture_in_a_graph_with_key_ranges():
         torch.cuda.synchronize()
         assert torch.equal(o, eager)
         assert torch.equal(pa.attn_fwd(q, k, v, causal=True), eager)
+
+
+def test_runs_without_memory_for_the_workspace():
+    case = (1, 32, 8, 64, 16000, 128, "f16", True, False, None, None)
+    assert _ranges(case) > 1
+    q, k, v, _ = _inputs(case)
+    q, k, v = q.cuda(), k.cuda(), v.cuda()
+    ref, o = pa.attn_fwd(q, k, v, causal=True), torch.empty_like(q)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    held = torch.cuda.memory_reserved()
+    try:                                     # the allocator refuses what is past what it holds now
+        torch.cuda.set_per_process_memory_fraction(held / torch.cuda.get_device_properties(0).total_memory)
+        assert pa.attn_fwd(q, k, v, o, causal=True) is o
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert_close(host32(o), host32(ref), "prefill without a workspace")
