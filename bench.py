@@ -53,7 +53,7 @@ HEADLINE = "causal_mha_prefill"
 METRIC = "prefill attn TFLOP/s (% MFMA peak); decode KV-read GB/s (% HBM peak)"
 PROFILES = os.path.join(ROOT, "profiles")
 KERNEL_SOURCES = {
-    "prefill": ["prefill.hip", "kernel_common.h", "launch.h"],
+    "prefill": ["prefill.hip", "prefill_split.hip", "kernel_common.h", "launch.h"],
     "decode": ["decode.hip", "kernel_common.h", "launch.h"],
     "norms": ["norms.hip", "kernel_common.h", "launch.h"],
 }
