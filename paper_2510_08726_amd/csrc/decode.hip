@@ -499,7 +499,7 @@ __global__ __launch_bounds__(kThreads) void decode_combine_kernel(DecodeParams p
     float m[kBatch], l[kBatch];
     f32x4 v[kBatch];
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u) {   // past the last chunk: that chunk again, with weight 0
+    for (int u = 0; u < kBatch; ++u) {   // past the last chunk: that chunk again, left out below
       const int s = min(s0 + u * NG, S - 1);
       v[u] = op[(size_t)s * CH];
       m[u] = mp[s];
@@ -515,9 +515,12 @@ __global__ __launch_bounds__(kThreads) void decode_combine_kernel(DecodeParams p
     M = mn;
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      const float w = (s0 + u * NG < S && m[u] != kNegInf) ? fast_exp2((m[u] - mn) * kLog2e) : 0.f;
+      // A repeat is left out by its values, not by its weight: 0 times an
+      // infinite value would be NaN.
+      const bool in = s0 + u * NG < S;
+      const float w = (in && m[u] != kNegInf) ? fast_exp2((m[u] - mn) * kLog2e) : 0.f;
       L = __builtin_fmaf(w, l[u], L);
-      acc += w * v[u];
+      acc += w * (in ? v[u] : f32x4{0.f, 0.f, 0.f, 0.f});
     }
   }
   sh_o[g][ch] = acc;

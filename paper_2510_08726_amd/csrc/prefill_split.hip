@@ -361,7 +361,7 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(PrefillParams p) {
     f32x4 v[kBatch];
     float2 w[kBatch];
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u) {   // past the last range: that range again, with weight 0
+    for (int u = 0; u < kBatch; ++u) {   // past the last range: that range again, left out below
       const size_t r = min(s0 + u, p.splits - 1) * nr + row;
       v[u] = *reinterpret_cast<const f32x4*>(p.ws + r * D + 4 * ch);
       w[u] = *reinterpret_cast<const float2*>(ml + 2 * r);
@@ -375,9 +375,11 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(PrefillParams p) {
     M = mn;
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      const float f = s0 + u < p.splits ? fast_exp2(w[u].x - mn) : 0.f;
+      // (By its values, not by its weight: 0 times an infinite value would be NaN.)
+      const bool in = s0 + u < p.splits;
+      const float f = in ? fast_exp2(w[u].x - mn) : 0.f;
       L = __builtin_fmaf(w[u].y, f, L);
-      acc += f * v[u];
+      acc += f * (in ? v[u] : f32x4{0.f, 0.f, 0.f, 0.f});
     }
   }
   const float inv = L > 0.f ? 1.f / L : 0.f;

@@ -50,3 +50,20 @@ def test_workspace_kept_from_a_smaller_chunk_count():
     if kept > 1:
         with pytest.raises(pa.AttnError):
             pa.attn_decode(q, k, v, workspace=ws[:ws.numel() - 256])
+
+
+@pytest.mark.parametrize("case", [(1, 4, 2, 2500, 128, 7), (1, 4, 4, 700, 64, 3), (2, 8, 2, 90, 64, 90), (1, 4, 2, 2500, 64, 16)],
+                         ids=lambda c: "x".join(map(str, c)))
+def test_infinite_values_in_the_last_chunk(case):
+    """Chunk counts that leave lanes of the combine without a chunk: infinite
+    values stay infinite (every weight is above 0), the other dims are as
+    without them."""
+    B, Hq, Hkv, Lk, D, S = case
+    print(f"decode infinities {case}", flush=True)
+    q, k, v = random_tensors([(B, Hq, 1, D), (B, Hkv, Lk, D), (B, Hkv, Lk, D)], "f16", seed=Lk)
+    v[..., -1, 5], v[..., -1, 6] = float("inf"), float("-inf")
+    o = host32(pa.attn_decode(q.cuda(), k.cuda(), v.cuda(), num_splits=S))
+    assert (o[..., 5] == float("inf")).all() and (o[..., 6] == float("-inf")).all()
+    v[..., 5:7] = 0.0
+    o[..., 5:7] = 0.0
+    assert_close(o, oracle_fwd(q, k, v, scale=D ** -0.5, causal=True), f"decode infinities {case}")

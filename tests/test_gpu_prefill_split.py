@@ -140,3 +140,18 @@ def test_runs_without_memory_for_the_workspace():
     finally:
         torch.cuda.set_per_process_memory_fraction(1.0)
     assert_close(host32(o), host32(ref), "prefill without a workspace")
+
+
+def test_infinite_values_with_key_ranges():
+    """A number of key ranges that leaves lanes of the combine without one:
+    infinite values stay infinite (every row sees them, with a weight above 0),
+    the other dims are as without them."""
+    case = (1, 2, 1, 100, 5000, 128, "bf16", False, False, None, None)
+    assert _ranges(case) > 1 and _ranges(case) % 8 != 0
+    q, k, v, _ = _inputs(case)
+    v[..., -1, 5], v[..., -1, 6] = float("inf"), float("-inf")
+    o = host32(run_fwd(q, k, v, scale=0.05))
+    assert (o[..., 5] == float("inf")).all() and (o[..., 6] == float("-inf")).all()
+    v[..., 5:7] = 0.0
+    o[..., 5:7] = 0.0
+    assert_close(o, oracle_fwd(q, k, v, scale=0.05), "infinite values")
