@@ -70,8 +70,9 @@ typedef enum {
   ATTN_ERR_UNSUPPORTED = -3, /* head dim not 64 or 128, unknown dtype, or (attn_fwd_mod)
                                 softcap or window without the causal mask, or softcap
                                 together with ALiBi */
-  ATTN_ERR_WORKSPACE = -4,   /* decode workspace smaller than attn_decode_workspace_bytes(), or
-                                (attn_decode_noalloc) larger than ATTN_DECODE_NOALLOC_BYTES */
+  ATTN_ERR_WORKSPACE = -4,   /* decode or prefill workspace too small (see attn_decode and
+                                attn_fwd_split) or not aligned, or (attn_decode_noalloc)
+                                larger than ATTN_DECODE_NOALLOC_BYTES */
   ATTN_ERR_HIP = -5          /* a HIP launch failed; see attn_last_hip_error() */
 } attn_status;
 
@@ -186,7 +187,13 @@ int attn_decode_num_splits(int B, int Hq, int Hkv, int Lk, int D);
  *               be short, chunks past Lk are empty), or 0 for the heuristic.
  *   workspace   device buffer of at least attn_decode_workspace_bytes(B, Hq,
  *               D, resolved num_splits) bytes, 16-byte aligned; its contents
- *               after the call are the local partials described above.
+ *               after the call are the local partials described above.  With
+ *               num_splits = 0 and one query head per KV head (or more than
+ *               32), a buffer for one workgroup per compute unit also serves:
+ *               n = ceil(CUs / (B * Hkv * query-head groups)) chunks, at most
+ *               ceil(Lk / 256).  Where it is too small for the count that
+ *               attn_decode_num_splits returns, the call uses n chunks, and
+ *               the partials are laid out for n.
  *
  * Two kernels run on `stream`: the local split kernel, then the combine.
  * With one chunk (num_splits resolving to 1) the split kernel also writes O,

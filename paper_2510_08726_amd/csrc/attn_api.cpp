@@ -260,10 +260,12 @@ int attn_decode_mod(const void* Q, const void* K, const void* V, void* O,
   const int rc = decode_check(Q, K, V, O, B, Hq, Hkv, Lk, D, scale, softcap, num_splits, dtype, &S);
   if (rc != ATTN_OK) return rc;
   if (!workspace) return ATTN_ERR_NULL;
-  // A workspace kept for one chunk per compute unit still serves where the
-  // library would choose more.
-  if (num_splits == 0 && workspace_bytes < attn_decode_workspace_bytes(B, Hq, D, S)) {
-    const int group = Hq / Hkv;
+  // A workspace for one workgroup of the per-head kernel per compute unit
+  // still serves where the library would choose more chunks.  A smaller one is
+  // refused, and so is any short workspace of the grouped kernel.
+  const int group = Hq / Hkv;
+  if (num_splits == 0 && attn::decode_split_heads(group) != 0 &&
+      workspace_bytes < attn_decode_workspace_bytes(B, Hq, D, S)) {
     const int64_t units = (int64_t)B * Hkv * (group / decode_heads_per_block(group));
     S = std::min(S, clamp_splits((compute_units() + units - 1) / units, Lk, kMinChunk));
   }
