@@ -169,7 +169,8 @@ size_t attn_decode_workspace_bytes(int B, int Hq, int D, int num_splits);
  * heuristic), from the compute units of the current device (256 if it cannot
  * be queried).  With 2..32 query heads per KV head, served together by one
  * workgroup per (chunk, KV head, batch): the most chunks whose workgroups do
- * not outnumber the compute units, of at least 128 keys.  With one query head
+ * not outnumber the compute units, of at least 128 keys (at D = 64, where that
+ * makes chunks of at least 1200 keys: twice the compute units).  With one query head
  * per KV head (or more than 32), one workgroup per (chunk, KV head, batch,
  * query-head group): one workgroup per compute unit if that divides evenly,
  * else up to two, chunks of at least 256 keys.
@@ -188,12 +189,12 @@ int attn_decode_num_splits(int B, int Hq, int Hkv, int Lk, int D);
  *   workspace   device buffer of at least attn_decode_workspace_bytes(B, Hq,
  *               D, resolved num_splits) bytes, 16-byte aligned; its contents
  *               after the call are the local partials described above.  With
- *               num_splits = 0 and one query head per KV head (or more than
- *               32), a buffer for one workgroup per compute unit also serves:
- *               n = ceil(CUs / (B * Hkv * query-head groups)) chunks, at most
- *               ceil(Lk / 256).  Where it is too small for the count that
- *               attn_decode_num_splits returns, the call uses n chunks, and
- *               the partials are laid out for n.
+ *               num_splits = 0 a buffer for one workgroup per compute unit
+ *               also serves: for n = floor(CUs / (B * Hkv)) chunks of at least
+ *               128 keys with 2..32 query heads per KV head, else ceil(CUs /
+ *               (B * Hkv * query-head groups)) of at least 256.  Where it is
+ *               too small for the count that attn_decode_num_splits returns,
+ *               the call uses n chunks, and the partials are laid out for n.
  *
  * Two kernels run on `stream`: the local split kernel, then the combine.
  * With one chunk (num_splits resolving to 1) the split kernel also writes O,

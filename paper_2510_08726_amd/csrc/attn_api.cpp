@@ -23,6 +23,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr int64_t kMaxGrid = std::numeric_limits<int32_t>::max();
 constexpr int kMinChunk = 256;    // keys per decode chunk chosen by the heuristic (one head per KV head)
 constexpr int kMinChunkGrouped = 128;   // grouped heads: at least one 32-key tile per wave
+constexpr int kTwoChunks = 1200;        // grouped heads, D = 64: keys per chunk from which two share a compute unit
 
 bool shape_ok(int B, int Hq, int Hkv, int Lq, int Lk) {
   return B >= 1 && Hq >= 1 && Hkv >= 1 && Lq >= 1 && Lk >= 1 && Hq % Hkv == 0;
@@ -68,6 +69,16 @@ int decode_heads_per_block(int group) {
 // At most one chunk per `least` keys, at least one chunk.
 int clamp_splits(int64_t s, int Lk, int least) {
   return (int)std::max<int64_t>(std::min(s, ((int64_t)Lk + least - 1) / least), 1);
+}
+
+// Decode chunks of one workgroup per compute unit: the count below which no
+// workspace may fall (attn_decode_num_splits gives as many or more).  The
+// grouped kernel's is rounded down: all its workgroups run in one round.
+int one_round_splits(int B, int Hq, int Hkv, int Lk, int cus) {
+  const int group = Hq / Hkv, gh = attn::decode_split_heads(group);
+  if (gh == 0) return clamp_splits(cus / ((int64_t)B * Hkv), Lk, kMinChunkGrouped);
+  const int64_t units = (int64_t)B * Hkv * (group / gh);
+  return clamp_splits((cus + units - 1) / units, Lk, kMinChunk);
 }
 
 const char* dtype_name(attn_dtype dtype) { return dtype == ATTN_BF16 ? "bf16" : "f16"; }
@@ -179,12 +190,19 @@ int attn_decode_num_splits(int B, int Hq, int Hkv, int Lk, int D) {
   if (!shape_ok(B, Hq, Hkv, 1, Lk) || (D != 64 && D != 128)) return 0;
   const int group = Hq / Hkv, cus = compute_units();
   if (group >= 2 && group <= 32) {
-    // The grouped kernel: one workgroup per (chunk, KV head, batch), and with
-    // its LDS one workgroup at a time per compute unit (D = 128), so the most
-    // chunks that still run in one round: 6 x 64/8 heads, 4050 keys took 41
-    // us in 6 chunks (288 workgroups), 29 in 5; 13 x 32/8, 20000 keys 230 in 3
-    // and 170 in 2; 11 x 32/16, 3000 keys 63 in 2 and 53 in 1.
-    return clamp_splits(cus / ((int64_t)B * Hkv), Lk, kMinChunkGrouped);
+    // The grouped kernel: one workgroup per (chunk, KV head, batch).  At D =
+    // 128 its LDS (128 KB) lets one run at a time per compute unit, so the most
+    // chunks that still run in one round: 6 x 64/8 heads, 4050 keys took 41 us
+    // in 6 chunks (288 workgroups), 29 in 5; 13 x 32/8, 20000 keys 230 in 3 and
+    // 170 in 2; 11 x 32/16, 3000 keys 63 in 2 and 53 in 1.
+    const int one = one_round_splits(B, Hq, Hkv, Lk, cus);
+    // At D = 64 two run at a time, and one alone reads at about half their
+    // rate: up to two per compute unit, where their chunks are long enough to
+    // pay for more partials.  11 x 24/12 heads, 12222 keys took 134 us in 1
+    // chunk, 88 in 2; 92 KV heads, 15487 keys 99 us in 2, 79 in 3 and 63 in 5;
+    // but 16 KV heads, 4856 keys 13.0 in 16 and 13.4 in 32.
+    if (D == 64 && Lk / one >= kTwoChunks) return clamp_splits(2 * cus / ((int64_t)B * Hkv), Lk, kMinChunkGrouped);
+    return one;
   }
   // The per-head kernel: one workgroup per compute unit where the heads divide
   // them evenly (measured at steady clock with nontemporal K/V loads, batch
@@ -260,15 +278,10 @@ int attn_decode_mod(const void* Q, const void* K, const void* V, void* O,
   const int rc = decode_check(Q, K, V, O, B, Hq, Hkv, Lk, D, scale, softcap, num_splits, dtype, &S);
   if (rc != ATTN_OK) return rc;
   if (!workspace) return ATTN_ERR_NULL;
-  // A workspace for one workgroup of the per-head kernel per compute unit
-  // still serves where the library would choose more chunks.  A smaller one is
-  // refused, and so is any short workspace of the grouped kernel.
-  const int group = Hq / Hkv;
-  if (num_splits == 0 && attn::decode_split_heads(group) != 0 &&
-      workspace_bytes < attn_decode_workspace_bytes(B, Hq, D, S)) {
-    const int64_t units = (int64_t)B * Hkv * (group / decode_heads_per_block(group));
-    S = std::min(S, clamp_splits((compute_units() + units - 1) / units, Lk, kMinChunk));
-  }
+  // A workspace for one workgroup per compute unit still serves where the
+  // library would choose up to two; a smaller one is refused.
+  if (num_splits == 0 && workspace_bytes < attn_decode_workspace_bytes(B, Hq, D, S))
+    S = std::min(S, one_round_splits(B, Hq, Hkv, Lk, compute_units()));
   const size_t need = attn_decode_workspace_bytes(B, Hq, D, S);
   if (workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 15)) return ATTN_ERR_WORKSPACE;
   return decode_launch(Q, K, V, O, B, Hq, Hkv, Lk, D, scale, alibi_slopes, softcap, S, workspace, dtype, stream);

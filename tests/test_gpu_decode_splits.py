@@ -67,3 +67,24 @@ def test_infinite_values_in_the_last_chunk(case):
     v[..., 5:7] = 0.0
     o[..., 5:7] = 0.0
     assert_close(o, oracle_fwd(q, k, v, scale=D ** -0.5, causal=True), f"decode infinities {case}")
+
+
+@pytest.mark.parametrize("case", [(11, 24, 12, 1500, "f16"), (3, 64, 32, 2600, "bf16"), (1, 8, 2, 150000, "f16")],
+                         ids=lambda c: "x".join(map(str, c)))
+def test_grouped_chunks_at_head_dim_64(case):
+    """Two workgroups per compute unit (D = 64, long chunks), and a workspace
+    for one: each against the oracle."""
+    B, Hq, Hkv, Lk, dt = case
+    cu = _cus()
+    S, one = pa.attn_decode_num_splits(B, Hq, Hkv, Lk, 64), max(cu // (B * Hkv), 1)
+    print(f"decode D 64 {case} {S} chunks, {one}", flush=True)
+    if Lk / one >= 1200:
+        assert S == 2 * cu // (B * Hkv)
+    q, k, v = random_tensors([(B, Hq, 1, 64), (B, Hkv, Lk, 64), (B, Hkv, Lk, 64)], dt, seed=Lk)
+    ref = oracle_fwd(q, k, v, scale=0.125, causal=True)
+    q, k, v = q.cuda(), k.cuda(), v.cuda()
+    assert_close(host32(pa.attn_decode(q, k, v)), ref, f"decode {case}, {S} chunks")
+    ws = torch.empty(pa.attn_decode_workspace_bytes(B, Hq, 64, one), dtype=torch.uint8, device="cuda")
+    o = pa.attn_decode(q, k, v, workspace=ws)
+    assert torch.equal(o, pa.attn_decode(q, k, v, num_splits=one))
+    assert_close(host32(o), ref, f"decode {case}, {one} chunks")
