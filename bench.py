@@ -240,7 +240,8 @@ def run_workload(name, steps, warmup, *, splits=0, errors=False):
             return lambda: pa.attn_fwd(qs, ks, vs, o, causal=w.causal, scale=w.sm_scale, alibi_slopes=sl,
                                        softcap=w.softcap or None, window=w.window or None)
         work = prefill_flops(w.B, w.Hq, w.Lq, w.Lk, w.D, w.causal, w.window)
-        kernels = pa.attn_fwd_kernels(w.D, q.dtype, w.causal, sl is not None, w.softcap, w.window)
+        kernels = pa.attn_fwd_call_kernels(w.B, w.Hq, w.Hkv, w.Lq, w.Lk, w.D, q.dtype, w.causal, sl is not None,
+                                           w.softcap, w.window)
     fn = [step(*t) for t in sets]
     ms, wall_ms, each = time_steps(fn, steps, warmup)
     # One input read by every step (the last calls: o is then set 0's output).

@@ -251,12 +251,11 @@ int attn_decode_noalloc(const void* Q, const void* K, const void* V, void* O,
                         attn_dtype dtype, hipStream_t stream);
 
 /*
- * The kernels that attn_fwd_mod (attn_fwd: softcap = 0, window = 0) launches
- * for these arguments, written to buf as a NUL-terminated string such as
+ * The kernel that attn_fwd_mod (attn_fwd: softcap = 0, window = 0) launches
+ * for these arguments where the query rows give every compute unit work,
+ * written to buf as a NUL-terminated string such as
  * "prefill_kernel<128,f16,1,0,0,0>" (head dim, element type, then the
  * causal, ALiBi, SoftCap and window template flags).  Host only: no HIP call.
- * (A call whose query rows cannot give every compute unit a workgroup of that
- * kernel may run prefill_split_kernel<D,type,G,alibi,softcap> instead.)
  * For coverage checks and profiles of the rolling-update kernel (Section
  * "Rolling Update").  alibi: non-zero if slopes would be passed.
  * Errors: the argument errors of attn_fwd_mod; ATTN_ERR_SHAPE if buf is NULL
@@ -264,6 +263,19 @@ int attn_decode_noalloc(const void* Q, const void* K, const void* V, void* O,
  */
 int attn_fwd_kernels(int D, attn_dtype dtype, int causal, int alibi, float softcap, int window,
                      char* buf, size_t len);
+
+/*
+ * The kernels that a call of these sizes launches: attn_fwd_kernels' name, or,
+ * with few query rows, "prefill_split_kernel<128,bf16,4,0,0>" (head dim,
+ * element type, key groups per workgroup, then the ALiBi and SoftCap flags),
+ * and ";prefill_combine_kernel<128,bf16>" behind it for several key ranges.
+ * workspace: non-zero for an attn_fwd_split that is given one, 0 for attn_fwd
+ * and attn_fwd_mod.  Depends on the current device's compute units (256 if
+ * they cannot be queried).  Errors as attn_fwd_kernels, and ATTN_ERR_SHAPE for
+ * bad sizes.
+ */
+int attn_fwd_call_kernels(int B, int Hq, int Hkv, int Lq, int Lk, int D, attn_dtype dtype, int causal, int alibi,
+                          float softcap, int window, int workspace, char* buf, size_t len);
 
 /*
  * The kernels that attn_decode_mod (attn_decode: softcap = 0) launches, as

@@ -22,7 +22,8 @@ import torch
 __all__ = [
     "attn_fwd", "attn_fwd_mod", "attn_decode", "attn_decode_mod", "attn_decode_workspace_bytes",
     "attn_decode_num_splits", "attn_decode_noalloc", "peaks_hbm_read", "peaks_mfma", "peaks_mfma_waves",
-    "peaks_mfma_operand_bytes", "norm_chunks", "norm_kernels", "norm_workspace_bytes", "norm_l2", "rmsnorm_rowmax", "attn_fwd_kernels", "attn_decode_kernels",
+    "peaks_mfma_operand_bytes", "norm_chunks", "norm_kernels", "norm_workspace_bytes", "norm_l2", "rmsnorm_rowmax", "attn_fwd_kernels", "attn_fwd_call_kernels",
+    "attn_decode_kernels",
     "attn_status_string", "attn_last_hip_error", "library_path", "load_library", "AttnError",
     "ATTN_OK", "ATTN_ERR_NULL", "ATTN_ERR_SHAPE", "ATTN_ERR_UNSUPPORTED", "ATTN_ERR_WORKSPACE",
     "ATTN_ERR_HIP",
@@ -84,6 +85,8 @@ def load_library():
     lib.attn_decode_noalloc.restype = ci
     lib.attn_fwd_kernels.argtypes = [ci, ci, ci, ci, cf, ci, ctypes.c_char_p, cs]
     lib.attn_fwd_kernels.restype = ci
+    lib.attn_fwd_call_kernels.argtypes = [ci, ci, ci, ci, ci, ci, ci, ci, ci, cf, ci, ci, ctypes.c_char_p, cs]
+    lib.attn_fwd_call_kernels.restype = ci
     lib.attn_decode_kernels.argtypes = [ci, ci, ci, ci, ci, cf, ctypes.c_char_p, cs]
     lib.attn_decode_kernels.restype = ci
     lib.norm_kernels.argtypes = [ci, ci, ci, ci, ctypes.c_char_p, cs]
@@ -343,10 +346,21 @@ def attn_decode_noalloc(q, k, v, o=None, *, scale=None, alibi_slopes=None, softc
 
 
 def attn_fwd_kernels(D, dtype, causal, alibi, softcap=0.0, window=0):
-    """Names of the kernels attn_fwd_mod launches for these arguments (host only)."""
+    """Name of the kernel attn_fwd_mod launches for these arguments where the
+    query rows give every compute unit work (host only)."""
     buf = ctypes.create_string_buffer(256)
     _check(load_library().attn_fwd_kernels(D, _DTYPE_CODE.get(dtype, dtype), int(bool(causal)), int(bool(alibi)),
                                            float(softcap or 0.0), int(window or 0), buf, 256))
+    return buf.value.decode().split(";")
+
+
+def attn_fwd_call_kernels(B, Hq, Hkv, Lq, Lk, D, dtype, causal, alibi, softcap=0.0, window=0, workspace=True):
+    """Names of the kernels that attn_fwd launches for these sizes (host only;
+    workspace=False: those of the C entry points without one)."""
+    buf = ctypes.create_string_buffer(256)
+    _check(load_library().attn_fwd_call_kernels(B, Hq, Hkv, Lq, Lk, D, _DTYPE_CODE.get(dtype, dtype),
+                                                int(bool(causal)), int(bool(alibi)), float(softcap or 0.0),
+                                                int(window or 0), int(bool(workspace)), buf, 256))
     return buf.value.decode().split(";")
 
 

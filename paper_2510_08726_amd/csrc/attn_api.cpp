@@ -322,6 +322,22 @@ int attn_fwd_kernels(int D, attn_dtype dtype, int causal, int alibi, float softc
   return put(buf, len, s);
 }
 
+int attn_fwd_call_kernels(int B, int Hq, int Hkv, int Lq, int Lk, int D, attn_dtype dtype, int causal, int alibi,
+                          float softcap, int window, int workspace, char* buf, size_t len) {
+  if (!shape_ok(B, Hq, Hkv, Lq, Lk)) return ATTN_ERR_SHAPE;
+  char s[160];
+  const int rc = attn_fwd_kernels(D, dtype, causal, alibi, softcap, window, s, sizeof s);
+  if (rc != ATTN_OK) return rc;
+  const attn::PrefillSplitPlan plan = attn::prefill_split_plan(B, Hq, Hkv, Lq, Lk, D, causal != 0, window, compute_units(),
+                                                               workspace ? attn::kMaxPrefillSplits : 1);
+  if (plan.kgroups > 0) {
+    const int n = std::snprintf(s, sizeof s, "prefill_split_kernel<%d,%s,%d,%d,%d>", D, dtype_name(dtype), plan.kgroups,
+                                alibi ? 1 : 0, softcap > 0.f ? 1 : 0);
+    if (plan.splits > 1) std::snprintf(s + n, sizeof s - n, ";prefill_combine_kernel<%d,%s>", D, dtype_name(dtype));
+  }
+  return put(buf, len, s);
+}
+
 int attn_decode_kernels(int Hq, int Hkv, int D, attn_dtype dtype, int alibi, float softcap, char* buf, size_t len) {
   if (Hq < 1 || Hkv < 1 || Hq % Hkv != 0 || !std::isfinite(softcap) || softcap < 0.f) return ATTN_ERR_SHAPE;
   if (!dims_supported(D, dtype)) return ATTN_ERR_UNSUPPORTED;

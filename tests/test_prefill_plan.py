@@ -46,3 +46,22 @@ def test_workspace(lib):
     need = W(1, 32, 64, 128, 8)
     assert call(FAKE, need - 1) == pa.ATTN_ERR_WORKSPACE
     assert call(ctypes.c_void_p(0x10008), need) == pa.ATTN_ERR_WORKSPACE
+
+
+def test_the_names_are_of_the_kernels_that_run(lib):
+    """Many rows, few rows, and few rows on many keys with and without a
+    workspace."""
+    import torch
+    f16, bf16 = torch.float16, torch.bfloat16
+    K = pa.attn_fwd_call_kernels
+    assert K(4, 32, 32, 2048, 2048, 128, f16, 1, 0) == ["prefill_kernel<128,f16,1,0,0,0>"]
+    assert K(1, 32, 8, 500, 6100, 128, bf16, 1, 0) == ["prefill_split_kernel<128,bf16,4,0,0>"]
+    assert K(1, 32, 8, 64, 16000, 128, f16, 1, 1) == ["prefill_split_kernel<128,f16,4,1,0>",
+                                                      "prefill_combine_kernel<128,f16>"]
+    assert len(K(1, 32, 8, 64, 16000, 128, f16, 1, 1, workspace=False)) == 1
+    assert K(1, 32, 8, 64, 16000, 64, bf16, 1, 0, 30.0, 9000) == ["prefill_split_kernel<64,bf16,4,0,1>",
+                                                                 "prefill_combine_kernel<64,bf16>"]
+    for bad in ((0, 32, 8, 64, 64, 128, f16, 1, 0), (1, 32, 5, 64, 64, 128, f16, 1, 0), (1, 32, 8, 64, 64, 96, f16, 1, 0),
+                (1, 32, 8, 64, 64, 128, f16, 0, 0, 0.0, 7), (1, 32, 8, 64, 64, 128, f16, 1, 1, 3.0)):
+        with pytest.raises(pa.AttnError):
+            K(*bad)
