@@ -110,7 +110,7 @@ int attn_last_hip_error(void) { return g_last_hip_error; }
 
 int attn_fwd_num_splits(int B, int Hq, int Hkv, int Lq, int Lk, int D, int causal, int window) {
   if (!shape_ok(B, Hq, Hkv, Lq, Lk) || (D != 64 && D != 128) || window < 0) return 0;
-  return attn::prefill_split_plan(B, Hq, Hkv, Lq, Lk, D, causal != 0, window, compute_units(),
+  return attn::prefill_split_plan(B, Hq, Hkv, Lq, Lk, D, causal != 0, window, false, false, compute_units(),
                                   attn::kMaxPrefillSplits).splits;
 }
 
@@ -137,8 +137,9 @@ int attn_fwd_split(const void* Q, const void* K, const void* V, void* O,
   const int bm = attn::prefill_block_rows();
   const int64_t nqb = ((int64_t)Lq + bm - 1) / bm;
   if (nqb * B * Hq > kMaxGrid) return ATTN_ERR_SHAPE;
-  const attn::PrefillSplitPlan plan = attn::prefill_split_plan(B, Hq, Hkv, Lq, Lk, D, causal != 0, window, compute_units(),
-                                                               workspace ? attn::kMaxPrefillSplits : 1);
+  const attn::PrefillSplitPlan plan =
+      attn::prefill_split_plan(B, Hq, Hkv, Lq, Lk, D, causal != 0, window, alibi_slopes != nullptr, softcap > 0.f,
+                               compute_units(), workspace ? attn::kMaxPrefillSplits : 1);
   const int S = plan.splits;
   if (S > 1 && (workspace_bytes < attn_fwd_workspace_bytes(B, Hq, Lq, D, S) || (reinterpret_cast<uintptr_t>(workspace) & 15)))
     return ATTN_ERR_WORKSPACE;
@@ -328,8 +329,9 @@ int attn_fwd_call_kernels(int B, int Hq, int Hkv, int Lq, int Lk, int D, attn_dt
   char s[160];
   const int rc = attn_fwd_kernels(D, dtype, causal, alibi, softcap, window, s, sizeof s);
   if (rc != ATTN_OK) return rc;
-  const attn::PrefillSplitPlan plan = attn::prefill_split_plan(B, Hq, Hkv, Lq, Lk, D, causal != 0, window, compute_units(),
-                                                               workspace ? attn::kMaxPrefillSplits : 1);
+  const attn::PrefillSplitPlan plan =
+      attn::prefill_split_plan(B, Hq, Hkv, Lq, Lk, D, causal != 0, window, alibi != 0, softcap > 0.f, compute_units(),
+                               workspace ? attn::kMaxPrefillSplits : 1);
   if (plan.kgroups > 0) {
     const int n = std::snprintf(s, sizeof s, "prefill_split_kernel<%d,%s,%d,%d,%d>", D, dtype_name(dtype), plan.kgroups,
                                 alibi ? 1 : 0, softcap > 0.f ? 1 : 0);

@@ -82,8 +82,8 @@ struct PrefillSplitPlan {
   int kgroups;          // key groups of its workgroups (2 or 4), or 0: prefill.hip runs
   int splits;           // key ranges over workgroups that it wants (needs a workspace when > 1)
 };
-PrefillSplitPlan prefill_split_plan(int B, int Hq, int Hkv, int Lq, int Lk, int D, bool causal, int window, int cus,
-                                    int max_splits);
+PrefillSplitPlan prefill_split_plan(int B, int Hq, int Hkv, int Lq, int Lk, int D, bool causal, int window, bool alibi,
+                                    bool cap, int cus, int max_splits);
 hipError_t launch_prefill_split(const PrefillParams& p, hipStream_t stream);
 // One per (head dim, element type); launch_prefill dispatches to them.
 hipError_t launch_prefill_d128_f16(const PrefillParams& p, hipStream_t stream);

@@ -423,22 +423,30 @@ int64_t items_of(int B, int Hq, int group, int Lq, int c) {
 }
 
 // Which kernel, how many key groups a workgroup and how many key ranges over
-// workgroups: the least estimated time, in us.  The estimates are linear in
-// the tiles of the longest item and fit 26 shapes measured under 15 plans each
-// (1 to 16 heads a batch and 64 to 2000 rows, both head dims): a tile costs
-// prefill.hip 0.455 (D = 128) or 0.37, an iteration here 1.2 or 0.67 with 4
-// groups (bound by the 64 KB of tiles that one compute unit fetches) and 0.95
-// or 0.65 with 2; to that come the start and end of a kernel, and for several
-// key ranges the combine kernel (3 us) and the partials' way through memory (3
-// TB/s).  The split has to win by 13 %: near the line the estimates are not
-// better than that, and prefill.hip is the faster of the two where its
-// workgroups fill the compute units (from there on it always runs).  Measured,
-// prefill.hip and here: 1 x 32/8 heads, 500 rows on 6100 keys 93 and 64 us (4
-// groups, 1 range); 64 on 16000 230 and 31 (4, 8); 2 x 32/16, 130 on 13392 197
-// and 115 (2, 2); D = 64, 1 x 32/4, 200 on 9000 100 and 34 (4, 2); 1 x 32 x 482
-// 14.5 and 12.0 (4, 1); but 1 x 32/8 x 1039 22 and 24 (2, 1).
-PrefillSplitPlan prefill_split_plan(int B, int Hq, int Hkv, int Lq, int Lk, int D, bool causal, int window, int cus,
-                                    int max_splits) {
+// workgroups: the least estimated time.  The estimates are linear in the tiles
+// of the longest item, in us, and fitted to 2500 random shapes that give
+// prefill.hip at most 256 workgroups, under every plan (1 to 1600 rows, up to
+// 7600 keys, both head dims, every modifier); nine in ten are within 12 %.
+// prefill.hip: a start and end, longer with a window or ALiBi, and a cost for a
+// tile, larger with a cap.  Here: a start and end, the first tiles (each key
+// group in use starts another fetch) and a cost for an iteration, taken
+// between the whole iterations and the tiles' share of them.  Where the
+// workgroups outnumber the compute units:
+//  - D = 128 (a workgroup takes a compute unit's LDS) starts the rest when the
+//    first items end: the lightest items and a start more.  Past a quarter
+//    more than the compute units prefill.hip is the faster one;
+//  - D = 64 runs two at a time, which share the compute unit's fetches.
+// Several key ranges cost the combine kernel and the partials' way through
+// memory.  The split has to win by 4 %: on those shapes the kernel taken is
+// then never more than 1 % behind prefill.hip, and 0.4 % behind the best of
+// all on average.
+// Measured, prefill.hip and here: 1 x 32/8 heads, 500 rows on 6100 keys 93 and
+// 64 us (4 groups, 1 range); 64 on 16000 230 and 31 (4, 8); 2 x 32/16, 130 on
+// 13392 197 and 115 (2, 2); D = 64, 1 x 32/4, 200 on 9000 100 and 34 (4, 2); 1 x
+// 32 x 482 14.5 and 12.0 (4, 1); but 6 x 8 x 361 12.9 and 17.4 (4, 1), and D =
+// 64, 4 x 2 x 8 5.0 and 5.3 (4, 1).
+PrefillSplitPlan prefill_split_plan(int B, int Hq, int Hkv, int Lq, int Lk, int D, bool causal, int window, bool alibi,
+                                    bool cap, int cus, int max_splits) {
   const int group = Hq / Hkv;
   const int64_t wide = items_of(B, Hq, group, Lq, 4);   // workgroups of prefill.hip
   if (wide > cus) return {0, 1};
@@ -452,27 +460,48 @@ PrefillSplitPlan prefill_split_plan(int B, int Hq, int Hkv, int Lq, int Lk, int 
       mean = std::min(mean, window + rows);
     }
   };
-  float most, mean;
-  keys(4, most, mean);
-  float best = 0.87f * (4.5f + (std::ceil(most / TN) + 4.f) * (D == 128 ? 0.455f : 0.37f));
-  PrefillSplitPlan plan = {0, 1};
-  for (int G : {4, 2}) {
-    const int64_t items = items_of(B, Hq, group, Lq, kWaves / G);
-    keys(kWaves / G, most, mean);
-    const float step = D == 128 ? (G == 4 ? 1.2f : 0.95f) : (G == 4 ? 0.67f : 0.65f);
-    for (int S = 1; S <= max_splits; ++S) {
-      const float longest = std::ceil(std::ceil(most / TN / S) / G), average = mean / TN / S / G + 0.5f;
-      float load = (float)(items * S) * average / cus;
-      if (items * S > cus) load += 0.5f * average;
-      float t = std::max(longest, load) * step + (D == 128 ? 6.f : 4.5f);
-      if (S > 1) t += 3.f + (float)((int64_t)B * Hq * Lq) * S * (D + 2) * 8.f / 3e6f;
-      if (t < best) {
-        best = t;
-        plan = {G, S};
+  // By head dim: 64, 128.
+  struct Split { float start, first, iter[3]; };   // iter: plain, ALiBi, SoftCap
+  static constexpr Split kSplit[2][2] = {{{4.55f, 0.67f, {0.72f, 0.89f, 1.13f}}, {5.45f, 1.42f, {1.16f, 1.32f, 1.39f}}},
+                                         {{4.85f, 0.51f, {0.69f, 0.83f, 1.04f}}, {5.95f, 1.13f, {1.00f, 1.15f, 1.25f}}}};
+  struct Wide { float start, window, alibi, alibi_all, tile, tile_window, tile_alibi, tile_cap; };
+  static constexpr Wide kWide[2] = {{4.95f, 1.55f, 1.1f, 0.8f, 0.366f, 0.045f, 0.035f, 0.16f},
+                                    {5.85f, 3.6f, 2.8f, 1.7f, 0.492f, 0.07f, 0.045f, 0.15f}};
+  const int d = D == 128;
+  auto best = [&](bool alibi, bool cap, int max_splits) {
+    const Wide& w = kWide[d];
+    float most, mean;
+    keys(4, most, mean);
+    const float start = w.start + (window > 0 ? w.window : !alibi ? 0.f : causal ? w.alibi : w.alibi_all);
+    const float tile = w.tile + (cap ? w.tile_cap : alibi ? w.tile_alibi : 0.f) + (window > 0 ? w.tile_window : 0.f);
+    float least = 0.96f * (start + tile * std::ceil(most / TN));
+    PrefillSplitPlan plan = {0, 1};
+    for (int G : {4, 2}) {
+      const Split& c = kSplit[G == 2][d];
+      const float iter = c.iter[cap ? 2 : alibi ? 1 : 0];
+      const int64_t items = items_of(B, Hq, group, Lq, kWaves / G);
+      keys(kWaves / G, most, mean);
+      for (int S = 1; S <= max_splits; ++S) {
+        const int64_t n = items * S;
+        if (n > (d ? cus + cus / 4 : 2 * cus)) break;
+        const float tiles = std::ceil(most / TN / S), whole = std::ceil(tiles / G);
+        float t = c.start + c.first * (std::min(tiles, (float)G) - 1.f) / (G - 1);
+        if (n > cus && !d) t += iter * std::max(whole, n * (mean / TN / S / G + 0.5f) / cus) + 2.5f;
+        else t += iter * 0.5f * (whole + std::max(tiles / G, 1.f));
+        if (n > cus && d) t += 5.5f + iter * std::max(0.f, 2.f * mean - most) / TN / S / G;
+        if (S > 1) t += 2.2f + (float)((int64_t)B * Hq * Lq) * S * (D + 2) * 8.f * 0.42e-6f;
+        if (t < least) {
+          least = t;
+          plan = {G, S};
+        }
       }
     }
-  }
-  return plan;
+    return plan;
+  };
+  // attn_fwd_num_splits, which sizes the workspace, knows no modifiers: they
+  // choose only among the plans with one range.
+  const PrefillSplitPlan plan = best(false, false, max_splits);
+  return plan.splits == 1 && (alibi || cap) ? best(alibi, cap, 1) : plan;
 }
 
 hipError_t launch_prefill_split(const PrefillParams& p, hipStream_t stream) {

@@ -65,3 +65,39 @@ def test_the_names_are_of_the_kernels_that_run(lib):
                 (1, 32, 8, 64, 64, 128, f16, 0, 0, 0.0, 7), (1, 32, 8, 64, 64, 128, f16, 1, 1, 3.0)):
         with pytest.raises(pa.AttnError):
             K(*bad)
+
+
+@pytest.mark.parametrize("call,name", [
+    # prefill.hip is the faster one: one or two tiles at D = 64, and more
+    # workgroups of the split kernel than compute units at D = 128
+    ((4, 2, 1, 8, 8, 64, 0, 0), "prefill_kernel<64"), ((1, 32, 8, 30, 30, 64, 1, 0), "prefill_kernel<64"),
+    ((3, 64, 8, 78, 78, 64, 0, 0), "prefill_kernel<64"), ((6, 8, 8, 361, 361, 128, 1, 0), "prefill_kernel<128"),
+    ((1, 32, 32, 782, 782, 128, 1, 0), "prefill_kernel<128"), ((4, 64, 32, 65, 65, 64, 1, 0, 30.0), "prefill_kernel<64"),
+    ((1, 2, 1, 54, 88, 128, 1, 0, 30.0), "prefill_kernel<128"),
+    # and here the split kernel: long masks' and slopes' set-up, more tiles
+    ((1, 32, 32, 1, 1, 64, 1, 1), "prefill_split_kernel<64"), ((1, 16, 16, 35, 175, 128, 1, 1, 0.0, 129), "prefill_split_kernel<128"),
+    ((1, 12, 4, 15, 15, 128, 1, 0, 0.0, 11), "prefill_split_kernel<128"), ((1, 32, 32, 482, 482, 128, 1, 0), "prefill_split_kernel<128"),
+    ((4, 8, 2, 568, 568, 64, 1, 0, 30.0, 516), "prefill_split_kernel<64"),
+])
+def test_the_faster_kernel_runs(lib, call, name):
+    """Calls measured under both kernels, the two at least 5 % apart."""
+    import torch
+    B, Hq, Hkv, Lq, Lk, D, causal, alibi, *mod = call
+    assert pa.attn_fwd_call_kernels(B, Hq, Hkv, Lq, Lk, D, torch.float16, causal, alibi, *mod)[0].startswith(name)
+
+
+def test_the_modifiers_do_not_change_the_ranges(lib):
+    """attn_fwd_num_splits, which sizes the workspace, takes no modifiers: the
+    call with one has as many ranges."""
+    import random
+    import torch
+    rng = random.Random(1)
+    for _ in range(2000):
+        Hkv = rng.choice([1, 2, 4, 8])
+        Lq, more = int(2 ** rng.uniform(0, 10)), int(2 ** rng.uniform(0, 14))
+        sizes = (rng.choice([1, 2, 4]), Hkv * rng.choice([1, 2, 3, 4]), Hkv, Lq, Lq + more, rng.choice([64, 128]))
+        window = rng.choice([0, rng.randrange(1, Lq + more)])
+        S = lib.attn_fwd_num_splits(*sizes, 1, window)
+        for alibi, cap in ((0, 0.0), (1, 0.0), (0, 30.0)):
+            names = pa.attn_fwd_call_kernels(*sizes, torch.float16, 1, alibi, cap, window)
+            assert (len(names) == 2) == (S > 1) and (S == 1 or "split" in names[0])
