@@ -424,22 +424,25 @@ int64_t items_of(int B, int Hq, int group, int Lq, int c) {
 
 // Which kernel, how many key groups a workgroup and how many key ranges over
 // workgroups: the least estimated time.  The estimates are linear in the tiles
-// of the longest item, in us, and fitted to 2500 random shapes that give
-// prefill.hip at most 256 workgroups, under every plan (1 to 1600 rows, up to
-// 7600 keys, both head dims, every modifier); nine in ten are within 12 %.
+// of the longest item, in us, and fitted to 4000 random shapes that give
+// prefill.hip at most 256 workgroups, under all plans (1 to 5000 rows, up to
+// 20000 keys, both head dims, every modifier); nine in ten are within 12 %.
 // prefill.hip: a start and end, longer with a window or ALiBi, and a cost for a
 // tile, larger with a cap.  Here: a start and end, the first tiles (each key
 // group in use starts another fetch) and a cost for an iteration, taken
 // between the whole iterations and the tiles' share of them.  Where the
 // workgroups outnumber the compute units:
-//  - D = 128 (a workgroup takes a compute unit's LDS) starts the rest when the
-//    first items end: the lightest items and a start more.  Past a quarter
-//    more than the compute units prefill.hip is the faster one;
-//  - D = 64 runs two at a time, which share the compute unit's fetches.
-// Several key ranges cost the combine kernel and the partials' way through
-// memory.  The split has to win by 4 %: on those shapes the kernel taken is
-// then never more than 1 % behind prefill.hip, and 0.4 % behind the best of
-// all on average.
+//  - D = 128 (a workgroup takes a compute unit's LDS) starts the others as the
+//    first end: a start more, and the longest item behind the first to end,
+//    later items of a unit behind later ones (several ranges go there only
+//    where even two of the fewest items don't fit one round);
+//  - D = 64 runs two at a time, which share the compute unit's fetches: the
+//    items of a compute unit one after another, half of a last incomplete
+//    round where they are alike.
+// Several key ranges cost the combine kernel, one latency for 8 of them, and
+// the partials' way through memory.  The split has to win by 4 %: on those
+// shapes the kernel taken is then never more than 3 % behind prefill.hip, and
+// on average 0.6 % behind the best of all.
 // Measured, prefill.hip and here: 1 x 32/8 heads, 500 rows on 6100 keys 93 and
 // 64 us (4 groups, 1 range); 64 on 16000 230 and 31 (4, 8); 2 x 32/16, 130 on
 // 13392 197 and 115 (2, 2); D = 64, 1 x 32/4, 200 on 9000 100 and 34 (4, 2); 1 x
@@ -450,15 +453,22 @@ PrefillSplitPlan prefill_split_plan(int B, int Hq, int Hkv, int Lq, int Lk, int 
   const int group = Hq / Hkv;
   const int64_t wide = items_of(B, Hq, group, Lq, 4);   // workgroups of prefill.hip
   if (wide > cus) return {0, 1};
-  // Keys of the longest and of the average item.
-  auto keys = [&](int c, float& most, float& mean) {
-    const float rows = 32.f * (c / heads_per_item(group, c));
-    most = mean = (float)Lk;
-    if (causal) mean -= 0.5f * std::min(Lq, Lk);
-    if (window > 0) {
-      most = std::min(most, window + rows);
-      mean = std::min(mean, window + rows);
+  // Keys of the longest, the average and the lightest item with c column blocks.
+  struct Keys { float most, mean, light; };
+  auto keys = [&](int c) {
+    Keys k = {(float)Lk, 0.f, (float)Lk};
+    float grow = 0.f;                                    // share of the rows that see more keys than the one before
+    if (causal) {
+      k.light = std::max(0.f, (float)Lk - Lq);
+      grow = 1.f;
     }
+    if (window > 0) {
+      k.most = std::min(k.most, (float)window + 32 * (c / heads_per_item(group, c)));
+      k.light = std::min(k.light, k.most);
+      grow = std::min(1.f, std::max(0.f, (float)window - ((float)Lk - Lq)) / Lq);
+    }
+    k.mean = k.most - 0.5f * grow * (k.most - k.light);
+    return k;
   };
   // By head dim: 64, 128.
   struct Split { float start, first, iter[3]; };   // iter: plain, ALiBi, SoftCap
@@ -470,26 +480,34 @@ PrefillSplitPlan prefill_split_plan(int B, int Hq, int Hkv, int Lq, int Lk, int 
   const int d = D == 128;
   auto best = [&](bool alibi, bool cap, int max_splits) {
     const Wide& w = kWide[d];
-    float most, mean;
-    keys(4, most, mean);
     const float start = w.start + (window > 0 ? w.window : !alibi ? 0.f : causal ? w.alibi : w.alibi_all);
     const float tile = w.tile + (cap ? w.tile_cap : alibi ? w.tile_alibi : 0.f) + (window > 0 ? w.tile_window : 0.f);
-    float least = 0.96f * (start + tile * std::ceil(most / TN));
+    float least = 0.96f * (start + tile * std::ceil(keys(4).most / TN));
     PrefillSplitPlan plan = {0, 1};
     for (int G : {4, 2}) {
       const Split& c = kSplit[G == 2][d];
       const float iter = c.iter[cap ? 2 : alibi ? 1 : 0];
       const int64_t items = items_of(B, Hq, group, Lq, kWaves / G);
-      keys(kWaves / G, most, mean);
+      const Keys k = keys(kWaves / G);
+      const float alike = k.light / k.most;
+      const int unit = (int)(items / ((int64_t)B * Hq / heads_per_item(group, kWaves / G)));   // items of a unit
       for (int S = 1; S <= max_splits; ++S) {
         const int64_t n = items * S;
-        if (n > (d ? cus + cus / 4 : 2 * cus)) break;
-        const float tiles = std::ceil(most / TN / S), whole = std::ceil(tiles / G);
+        if (d && n > (S > 1 && 2 * wide <= cus ? cus : 2 * cus)) break;
+        const float tiles = std::ceil(k.most / TN / S), whole = std::ceil(tiles / G);
         float t = c.start + c.first * (std::min(tiles, (float)G) - 1.f) / (G - 1);
-        if (n > cus && !d) t += iter * std::max(whole, n * (mean / TN / S / G + 0.5f) / cus) + 2.5f;
-        else t += iter * 0.5f * (whole + std::max(tiles / G, 1.f));
-        if (n > cus && d) t += 5.5f + iter * std::max(0.f, 2.f * mean - most) / TN / S / G;
-        if (S > 1) t += 2.2f + (float)((int64_t)B * Hq * Lq) * S * (D + 2) * 8.f * 0.42e-6f;
+        if (n > cus && !d) {
+          const float rounds = (float)n / cus;
+          const float per = rounds + 0.25f * (1.f - alike) + 0.5f * alike * (std::ceil(rounds) - rounds);
+          t += iter * std::max(whole, per * (k.mean / TN / S / G + 0.8f)) + 1.f;
+        } else {
+          t += iter * 0.5f * (whole + std::max(tiles / G, 1.f));
+        }
+        if (n > cus && d) {
+          const float later = std::min(1.f, (float)((n - cus - 1) / unit * unit) / cus);
+          t += 7.f + iter * (k.light + (k.most - k.light) * later) / TN / S / G;
+        }
+        if (S > 1) t += 1.1f + 0.8f * ((S + 7) / 8) + (float)((int64_t)B * Hq * Lq) * S * (D + 2) * 8.f * 0.385e-6f;
         if (t < least) {
           least = t;
           plan = {G, S};
