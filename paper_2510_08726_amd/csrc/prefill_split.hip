@@ -433,9 +433,9 @@ int64_t items_of(int B, int Hq, int group, int Lq, int c) {
 // between the whole iterations and the tiles' share of them.  Where the
 // workgroups outnumber the compute units:
 //  - D = 128 (a workgroup takes a compute unit's LDS) starts the others as the
-//    first end: a start more, and the longest item behind the first to end,
-//    later items of a unit behind later ones (several ranges go there only
-//    where even two of the fewest items don't fit one round);
+//    first end, within each XCD's share of the items: the longest of them, and
+//    a start and end more (several ranges go there only where even two of the
+//    fewest items don't fit one round);
 //  - D = 64 runs two at a time, which share the compute unit's fetches: the
 //    items of a compute unit one after another, half of a last incomplete
 //    round where they are alike.
@@ -453,21 +453,25 @@ PrefillSplitPlan prefill_split_plan(int B, int Hq, int Hkv, int Lq, int Lk, int 
   const int group = Hq / Hkv;
   const int64_t wide = items_of(B, Hq, group, Lq, 4);   // workgroups of prefill.hip
   if (wide > cus) return {0, 1};
-  // Keys of the longest, the average and the lightest item with c column blocks.
-  struct Keys { float most, mean, light; };
+  // Keys of the longest, the average and the lightest item with c column
+  // blocks; `grow` of a unit's items see fewer keys than the one before.
+  struct Keys {
+    float most, mean, light, grow;
+    // Keys of the item at the fraction f of a unit, heaviest first.
+    float at(float f) const { return f <= 1.f - grow ? most : light + (most - light) * std::max(0.f, 1.f - f) / grow; }
+  };
   auto keys = [&](int c) {
-    Keys k = {(float)Lk, 0.f, (float)Lk};
-    float grow = 0.f;                                    // share of the rows that see more keys than the one before
+    Keys k = {(float)Lk, 0.f, (float)Lk, 0.f};
     if (causal) {
       k.light = std::max(0.f, (float)Lk - Lq);
-      grow = 1.f;
+      k.grow = 1.f;
     }
     if (window > 0) {
       k.most = std::min(k.most, (float)window + 32 * (c / heads_per_item(group, c)));
       k.light = std::min(k.light, k.most);
-      grow = std::min(1.f, std::max(0.f, (float)window - ((float)Lk - Lq)) / Lq);
+      k.grow = std::min(1.f, std::max(0.f, (float)window - ((float)Lk - Lq)) / Lq);
     }
-    k.mean = k.most - 0.5f * grow * (k.most - k.light);
+    k.mean = k.most - 0.5f * k.grow * (k.most - k.light);
     return k;
   };
   // By head dim: 64, 128.
@@ -490,24 +494,33 @@ PrefillSplitPlan prefill_split_plan(int B, int Hq, int Hkv, int Lq, int Lk, int 
       const int64_t items = items_of(B, Hq, group, Lq, kWaves / G);
       const Keys k = keys(kWaves / G);
       const float alike = k.light / k.most;
-      const int unit = (int)(items / ((int64_t)B * Hq / heads_per_item(group, kWaves / G)));   // items of a unit
+      const float unit = (float)items / ((int64_t)B * Hq / heads_per_item(group, kWaves / G));   // items of a unit
       for (int S = 1; S <= max_splits; ++S) {
         const int64_t n = items * S;
         if (d && n > (S > 1 && 2 * wide <= cus ? cus : 2 * cus)) break;
         const float tiles = std::ceil(k.most / TN / S), whole = std::ceil(tiles / G);
-        float t = c.start + c.first * (std::min(tiles, (float)G) - 1.f) / (G - 1);
+        const float begin = c.start + c.first * (std::min(tiles, (float)G) - 1.f) / (G - 1);
+        float t;
         if (n > cus && !d) {
           const float rounds = (float)n / cus;
           const float per = rounds + 0.25f * (1.f - alike) + 0.5f * alike * (std::ceil(rounds) - rounds);
-          t += iter * std::max(whole, per * (k.mean / TN / S / G + 0.8f)) + 1.f;
+          t = begin + iter * std::max(whole, per * (k.mean / TN / S / G + 0.8f)) + 1.f;
         } else {
-          t += iter * 0.5f * (whole + std::max(tiles / G, 1.f));
+          t = begin + iter * 0.5f * (whole + std::max(tiles / G, 1.f));
         }
         if (n > cus && d) {
-          const float later = std::min(1.f, (float)((n - cus - 1) / unit * unit) / cus);
-          t += 7.f + iter * (k.light + (k.most - k.light) * later) / TN / S / G;
+          // A share of n / 8 items on cus / 8 compute units: `more` of them wait.
+          const float more = (float)(n - cus) / kXcds, own = (float)cus / kXcds;
+          float two;                                     // keys of the waiting item and the one before it
+          if (S > 1) two = k.light + k.most;
+          else if (more + own < unit) two = 2.f * k.at(own / unit);   // the share is a part of one unit
+          else two = k.light + (more >= unit ? k.most + (k.most - k.light) * (more - unit) / own : k.at(1.f - more / unit));
+          t = std::max(t, begin + 7.5f + iter * two / TN / S / G);
         }
-        if (S > 1) t += 1.1f + 0.8f * ((S + 7) / 8) + (float)((int64_t)B * Hq * Lq) * S * (D + 2) * 8.f * 0.385e-6f;
+        if (S > 1) {
+          t += 1.1f + 0.8f * ((S + 7) / 8) + (float)((int64_t)B * Hq * Lq) * S * (D + 2) * 8.f * 0.385e-6f;
+          t *= 1.02f;                                    // one range where there is next to nothing between them
+        }
         if (t < least) {
           least = t;
           plan = {G, S};
