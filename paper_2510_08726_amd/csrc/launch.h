@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime_api.h>
 #include <stddef.h>
+#include <stdint.h>
 
 namespace attn {
 
@@ -24,12 +25,12 @@ struct PrefillParams {
   int nqb;              // query blocks per head
   int nheads;           // B * Hq, set by the launcher
   int nitems;           // nqb * nheads, set by the launcher
-  int nxcd;             // XCDs the workgroups are spread over, set by the launcher
+  int nxcd;             // shares of the items, each with its own workgroups: the XCDs, or 1; set by the launcher
   int hg;               // query heads per workgroup (sharing one KV head), set by the launcher
   int kgroups;          // key groups of prefill_split.hip (2 or 4), 0 for prefill.hip
   int splits;           // its key ranges (1: none)
   float* ws;            // its partials, for splits > 1: [splits, B*Hq*Lq, D], then (max, sum) [splits, B*Hq*Lq, 2]
-  int sorted;           // 1: an XCD's items go out heaviest first, set by the launcher
+  int sorted;           // 1: a share's items go out heaviest first, set by the launcher
 };
 
 struct DecodeParams {
@@ -73,6 +74,9 @@ inline int decode_split_heads(int group) {
 }
 
 int prefill_block_rows();
+// Order of the items of prefill.hip: 0 KV head major, 1 heaviest first within
+// each XCD's share, 2 heaviest first over all.
+int prefill_order(int nitems, int nqb, int slots, bool causal, int window, int Lk, int64_t kv_bytes);
 hipError_t launch_prefill(const PrefillParams& p, hipStream_t stream);
 // Few query rows: keys split inside the workgroup, and with a workspace over
 // workgroups (prefill_split.hip); launch_prefill takes it when the plan of the

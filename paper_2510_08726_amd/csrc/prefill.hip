@@ -1209,25 +1209,11 @@ hipError_t launch_t(const PrefillParams& p, hipStream_t stream) {
   q.nitems = q.nqb * (q.nheads / q.hg);
   if (q.nitems == 0) return hipSuccess;
   const int slots = kWgPerCu * compute_units();
-  int grid = std::min(q.nitems, slots);
-  q.nxcd = grid % kXcds == 0 ? kXcds : 1;
-  // Causal items differ in length.  The KV-head-major deal balances them only
-  // over whole pairs of rounds: 3 x 12 heads of 3086 tokens (D 64, 900 items on
-  // 512 workgroups) took 92 us, 65 dealt heaviest first; 4 x 32/8 x 1614 110
-  // and 95, 6 x 32 x 1720 218 and 195.  But heaviest first spreads the readers
-  // of one K/V head over the rounds: where an XCD's K and V (its share of the
-  // heads) are far larger than its 4 MB L2 and the rounds are many, the
-  // imbalance is small and the refetching costs more (7 x 32 x 2544, 37 MB an
-  // XCD, 9 rounds: 433 us and 465, with 0.75 and 2.3 GB read).  Nor is there
-  // anything to balance where a window far shorter than the keys makes the
-  // items alike (16 heads x 5183, window 393: 42.9 and 43.9).
-  const int64_t kv_xcd = (int64_t)p.B * p.Hkv * p.Lk * D * 2 * (int64_t)sizeof(T) / kXcds;
-  q.sorted = CAUSAL && slots % (2 * kXcds) == 0 && q.nitems % (2 * slots) != 0 &&
-             (q.nitems < 6 * slots || kv_xcd <= (int64_t)12 << 20) && (!WIN || 4 * (int64_t)p.window >= p.Lk);
-  if (q.sorted) {
-    grid = slots;
-    q.nxcd = kXcds;
-  }
+  const int64_t kv = (int64_t)p.B * p.Hkv * p.Lk * D * 2 * (int64_t)sizeof(T);
+  const int order = prefill_order(q.nitems, q.nqb, slots, CAUSAL, WIN ? p.window : 0, p.Lk, kv);
+  q.sorted = order != 0;
+  const int grid = q.sorted ? slots : std::min(q.nitems, slots);
+  q.nxcd = order == 2 || grid % kXcds != 0 ? 1 : kXcds;
   hipLaunchKernelGGL((prefill_kernel<D, T, CAUSAL, ALIBI, CAP, WIN>), dim3(grid), dim3(kThreads), 0, stream, q);
   return hipGetLastError();
 }
@@ -1259,6 +1245,34 @@ hipError_t launch_prefill_d64_bf16(const PrefillParams& p, hipStream_t s) { retu
 
 #if ATTN_PREFILL_SHARD == 0
 int prefill_block_rows() { return BM; }
+
+// Order of the items (nqb row blocks for each unit: KV head and head group):
+// 0 KV head major, 1 heaviest first within each XCD's share, 2 heaviest first
+// over all.  Causal items differ in length.  The KV-head-major deal balances
+// them only over whole pairs of rounds: 3 x 12 heads of 3086 tokens (D 64, 900
+// items on 512 workgroups) took 92 us, 65 dealt heaviest first; 4 x 32/8 x 1614
+// 110 and 95, 6 x 32 x 1720 218 and 195.  But heaviest first
+//  - has nothing to balance where every item has a compute unit to itself or
+//    every unit is one item; its set-up then costs 0.3 to 0.5 us (4 x 4 x 3, D
+//    64, SoftCap: 5.0 us and 5.4);
+//  - presumes alike shares: with fewer units than XCDs one share is a unit's
+//    heavy end and another its light end, and all items go out as one share (8
+//    x 4748, D 128, window 3265: 69.6 us KV head major, 90 in shares; 2 x 4/1 x
+//    4177, D 64: 27.7 and 37.5; the 220 such shapes measured take 0.94 to 1.08
+//    of KV head major in one share, 11 % less in the middle);
+//  - spreads the readers of one K/V head over the rounds: where an XCD's K and
+//    V (its share of the heads) are far larger than its 4 MB L2 and the rounds
+//    are many, the imbalance is small and the refetching costs more (7 x 32 x
+//    2544, 37 MB an XCD, 9 rounds: 433 us and 465, with 0.75 and 2.3 GB read);
+//  - has nothing to gain where a window far shorter than the keys makes the
+//    items alike (16 heads x 5183, window 393: 42.9 and 43.9).
+int prefill_order(int nitems, int nqb, int slots, bool causal, int window, int Lk, int64_t kv_bytes) {
+  if (!causal || slots % (2 * kXcds) != 0 || nitems % (2 * slots) == 0) return 0;
+  if (nitems <= slots / 2 || nqb == 1) return 0;
+  if (nitems >= 6 * slots && kv_bytes / kXcds > (int64_t)12 << 20) return 0;
+  if (window > 0 && 4 * (int64_t)window < Lk) return 0;
+  return nitems / nqb < kXcds ? 2 : 1;
+}
 
 hipError_t launch_prefill(const PrefillParams& p, hipStream_t stream) {
   if (p.kgroups > 0) return launch_prefill_split(p, stream);
