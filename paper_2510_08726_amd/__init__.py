@@ -73,6 +73,12 @@ def load_library():
     lib.attn_fwd.restype = ci
     lib.attn_fwd_mod.argtypes = [vp, vp, vp, vp, ci, ci, ci, ci, ci, ci, ci, cf, vp, cf, ci, ci, vp]
     lib.attn_fwd_mod.restype = ci
+    lib.attn_fwd_split.argtypes = [vp, vp, vp, vp, ci, ci, ci, ci, ci, ci, ci, cf, vp, cf, ci, vp, cs, ci, vp]
+    lib.attn_fwd_split.restype = ci
+    lib.attn_fwd_num_splits.argtypes = [ci, ci, ci, ci, ci, ci, ci, ci]
+    lib.attn_fwd_num_splits.restype = ci
+    lib.attn_fwd_workspace_bytes.argtypes = [ci, ci, ci, ci, ci]
+    lib.attn_fwd_workspace_bytes.restype = cs
     lib.attn_decode.argtypes = [vp, vp, vp, vp, ci, ci, ci, ci, ci, cf, vp, ci, vp, cs, ci, vp]
     lib.attn_decode.restype = ci
     lib.attn_decode_mod.argtypes = [vp, vp, vp, vp, ci, ci, ci, ci, ci, cf, vp, cf, ci, vp, cs, ci, vp]
@@ -206,29 +212,47 @@ def _fwd_args(q, k, v, o, alibi_slopes):
     return o
 
 
+def _fwd_workspace(q, Hkv, Lk, causal, window, stream):
+    """The workspace of a call whose keys are divided over workgroups, or None
+    (one range): allocated in the pool of the stream that it is used on, so
+    not where that stream is unknown to PyTorch or on another device."""
+    B, Hq, Lq, D = q.shape
+    lib = load_library()
+    S = lib.attn_fwd_num_splits(B, Hq, Hkv, Lq, Lk, D, int(bool(causal)), int(window or 0))
+    s = torch.cuda.current_stream() if stream is None else stream
+    if S <= 1 or not isinstance(s, torch.cuda.Stream) or s.device != q.device:
+        return None
+    try:
+        with torch.cuda.stream(s):
+            return torch.empty(lib.attn_fwd_workspace_bytes(B, Hq, Lq, D, S), dtype=torch.uint8, device=q.device)
+    except torch.cuda.OutOfMemoryError:
+        return None
+
+
 def attn_fwd(q, k, v, o=None, *, causal=False, scale=None, alibi_slopes=None, softcap=None,
              window=None, stream=None):
-    """O = softmax(Q K^T * scale + bias) V by the fused prefill kernel.
+    """O = softmax(Q K^T * scale + bias) V by the fused prefill kernels.
 
     q [B, Hq, Lq, D], k and v [B, Hkv, Lk, D] (float16 or bfloat16, contiguous,
     on the GPU); ``o`` is written if given, else allocated.  ``scale``
-    defaults to 1/sqrt(D).  ``softcap`` (cap > 0) and ``window`` (W >= 1)
-    select the score modifiers of ``attn_fwd_mod``; without them the call
-    goes to the C entry point ``attn_fwd``.  Returns ``o``.
+    defaults to 1/sqrt(D).  ``softcap`` (cap > 0) and ``window`` (W >= 1) are
+    the score modifiers of the C entry point ``attn_fwd_mod``.  Where the keys
+    of few query rows are divided over workgroups (``attn_fwd_split``), the
+    workspace is allocated here, and the call does without where memory has
+    run out.  Returns ``o``.
     """
     r = (_BINDING or _load_binding()).attn_fwd(q, k, v, o, causal, scale, alibi_slopes, softcap, window, stream)
     if r is not None:
         return _result(r)
-    if softcap or window:
-        return attn_fwd_mod(q, k, v, o, causal=causal, scale=scale, alibi_slopes=alibi_slopes,
-                            softcap=softcap, window=window, stream=stream)
     o = _fwd_args(q, k, v, o, alibi_slopes)
     B, Hq, Lq, D = q.shape
     Hkv, Lk = k.shape[1], k.shape[2]
     sc = 1.0 / math.sqrt(D) if scale is None else float(scale)
-    _check(load_library().attn_fwd(_ptr(q), _ptr(k), _ptr(v), _ptr(o), B, Hq, Hkv, Lq, Lk, D,
-                                   int(bool(causal)), sc, _ptr(alibi_slopes), _DTYPE_CODE[q.dtype],
-                                   _stream(stream)))
+    cap, win = float(softcap or 0.0), int(window or 0)
+    ws = _fwd_workspace(q, Hkv, Lk, causal, win, stream)
+    _check(load_library().attn_fwd_split(_ptr(q), _ptr(k), _ptr(v), _ptr(o), B, Hq, Hkv, Lq, Lk, D,
+                                         int(bool(causal)), sc, _ptr(alibi_slopes), cap, win, _ptr(ws),
+                                         0 if ws is None else ws.numel(), _DTYPE_CODE[q.dtype], _stream(stream)))
     return o
 
 
@@ -236,17 +260,8 @@ def attn_fwd_mod(q, k, v, o=None, *, causal=False, scale=None, alibi_slopes=None
                  window=None, stream=None):
     """attn_fwd with the SoftCap modifier (``softcap``: None or cap > 0) and the
     causal sliding window (``window``: None or W >= 1 keys per row)."""
-    r = (_BINDING or _load_binding()).attn_fwd(q, k, v, o, causal, scale, alibi_slopes, softcap, window, stream)
-    if r is not None:
-        return _result(r)
-    o = _fwd_args(q, k, v, o, alibi_slopes)
-    B, Hq, Lq, D = q.shape
-    Hkv, Lk = k.shape[1], k.shape[2]
-    sc = 1.0 / math.sqrt(D) if scale is None else float(scale)
-    _check(load_library().attn_fwd_mod(_ptr(q), _ptr(k), _ptr(v), _ptr(o), B, Hq, Hkv, Lq, Lk, D,
-                                       int(bool(causal)), sc, _ptr(alibi_slopes), float(softcap or 0.0),
-                                       int(window or 0), _DTYPE_CODE[q.dtype], _stream(stream)))
-    return o
+    return attn_fwd(q, k, v, o, causal=causal, scale=scale, alibi_slopes=alibi_slopes, softcap=softcap,
+                    window=window, stream=stream)
 
 
 def attn_decode_workspace_bytes(B, Hq, D, num_splits):

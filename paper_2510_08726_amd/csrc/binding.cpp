@@ -153,11 +153,12 @@ PyObject* py_attn_fwd(PyObject*, PyObject* const* x, Py_ssize_t n) {
   const void *q = a.q->data_ptr(), *k = a.k->data_ptr(), *v = a.v->data_ptr();
   void* o = a.o.data_ptr();
   // Few rows against many keys: a workspace, which lives on this stream like
-  // the call itself.  Where memory has run out the call does without it.
+  // the call itself (so not for tensors on another device).  Where memory has
+  // run out the call does without it.
   at::Tensor ws;
   size_t bytes = 0;
   const int S = attn_fwd_num_splits(a.B, a.Hq, a.Hkv, a.Lq, a.Lk, a.D, causal, window);
-  if (S > 1) {
+  if (S > 1 && a.q->device().index() == c10::hip::getCurrentHIPStream().device_index()) {
     bytes = attn_fwd_workspace_bytes(a.B, a.Hq, a.Lq, a.D, S);
     try {
       ws = at::empty({(int64_t)bytes}, a.q->options().dtype(at::kByte));

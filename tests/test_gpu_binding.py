@@ -5,6 +5,7 @@ stream, and calls from several threads."""
 
 import threading
 
+import numpy as np
 import pytest
 import torch
 
@@ -127,3 +128,45 @@ def test_current_stream_and_threads():
     torch.cuda.synchronize()
     y2, m2 = pa.rmsnorm_rowmax(x)
     assert torch.equal(y, y2) and torch.equal(m, m2)
+
+
+def test_key_ranges_on_every_path(monkeypatch):
+    """A call whose keys are divided over workgroups takes the same kernels,
+    and so has the same bits, however it comes: marshalled in C++, through the
+    Python checks, with a stream, with scalars of other types."""
+    q, k, v = _qkv(B=1, Hq=8, Hkv=2, Lq=33, Lk=5000, D=128, dt="bf16")
+    S = pa.load_library().attn_fwd_num_splits(1, 8, 2, 33, 5000, 128, 1, 0)
+    assert S > 1
+    ref = pa.attn_fwd(q, k, v, causal=True)
+    one = torch.empty_like(q)                                # one range: other bits
+    rc = pa.load_library().attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), one.data_ptr(), 1, 8, 2, 33, 5000, 128, 1,
+                                    128 ** -0.5, None, 1, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert rc == 0 and not torch.equal(ref, one)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    for fn in (pa.attn_fwd, pa.attn_fwd_mod):
+        got = [_in_python(monkeypatch, lambda: fn(q, k, v, causal=True)), fn(q, k, v, causal=1),
+               fn(q, k, v, causal=True, scale=np.float64(128 ** -0.5)), fn(q, k, v, causal=True, stream=s),
+               fn(torch.nn.Parameter(q, requires_grad=False), k, v, causal=True)]
+        s.synchronize()
+        for i, g in enumerate(got):
+            assert torch.equal(g, ref), i
+
+
+def test_key_ranges_without_memory_in_python(monkeypatch):
+    """The Python path does without the workspace too where it doesn't fit."""
+    q, k, v = _qkv(B=1, Hq=8, Hkv=2, Lq=33, Lk=5000, D=128)
+    ref = pa.attn_fwd(q, k, v, causal=True)
+    empty, o = torch.empty, torch.empty_like(q)
+
+    def refuse(*a, **kw):
+        if kw.get("dtype") is torch.uint8:
+            raise torch.cuda.OutOfMemoryError("no memory")
+        return empty(*a, **kw)
+
+    with monkeypatch.context() as m:
+        m.setattr(torch, "empty", refuse)
+        _in_python(monkeypatch, lambda: pa.attn_fwd(q, k, v, o, causal=True))
+    torch.cuda.synchronize()
+    assert (o.float() - ref.float()).abs().max() < 2e-3 and not torch.equal(o, ref)
