@@ -153,7 +153,9 @@ int attn_fwd_split(const void* Q, const void* K, const void* V, void* O,
   p.bf16 = dtype == ATTN_BF16;
   p.cap_k2 = softcap > 0.f ? 2.f / softcap : 0.f;
   p.cap_cl = softcap > 0.f ? softcap * kLog2e : 0.f;
-  p.window = window;
+  // A window of Lk keys or more masks nothing, and the kernels' row + Lk - Lq +
+  // 1 - window stays within an int.
+  p.window = std::min(window, Lk);
   if (alibi_slopes || softcap > 0.f) {
     p.c = scale * kLog2e;
     p.qsign = 0;

@@ -155,3 +155,18 @@ def test_infinite_values_with_key_ranges():
     v[..., 5:7] = 0.0
     o[..., 5:7] = 0.0
     assert_close(o, oracle_fwd(q, k, v, scale=0.05), "infinite values")
+
+
+@pytest.mark.parametrize("B", [1, 70])
+@pytest.mark.parametrize("mod", [dict(), dict(softcap=5.0), dict(alibi=True)], ids=str)
+def test_windows_past_the_keys(B, mod):
+    """A window of at least Lk keys is no window, up to the largest int, also
+    for rows before the first key (Lq > Lk): the split and the wide kernel."""
+    q, k, v = (t.cuda().repeat(B, 1, 1, 1) for t in random_tensors([(1, 4, 200, 64), (1, 4, 100, 64), (1, 4, 100, 64)], "f16", seed=8))
+    mod = dict(mod)
+    sl = alibi_slopes(4).cuda() if mod.pop("alibi", False) else None
+    ref = pa.attn_fwd(q, k, v, causal=True, alibi_slopes=sl, window=100, **mod)
+    plain = pa.attn_fwd(q, k, v, causal=True, alibi_slopes=sl, **mod)
+    assert (ref.float() - plain.float()).abs().max() < 4e-3
+    for window in (101, 1 << 20, 2 ** 31 - 1):
+        assert torch.equal(pa.attn_fwd(q, k, v, causal=True, alibi_slopes=sl, window=window, **mod), ref), window
