@@ -11,6 +11,7 @@ Each row is compared by itself, so that one wrong row in 32 shows."""
 import numpy as np
 import pytest
 
+import paper_2510_08726_amd as pa
 from paper_2510_08726_amd.workloads import alibi_slopes, random_tensors
 from gpu_common import host32, oracle_fwd, run_fwd
 
@@ -27,15 +28,27 @@ CASES = [  # B, Hq, Hkv, Lq, Lk, D, dtype, alibi, softcap, window
 ]
 
 
+# The batch is repeated until the items outnumber the compute units, so that
+# prefill_kernel runs; as they are, the small cases run the split kernel.
+WIDE = 140
+
+
+@pytest.mark.parametrize("wide", [True, False], ids=["wide", "small"])
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
-def test_rows_that_see_nothing_of_the_first_tile(case):
+def test_rows_that_see_nothing_of_the_first_tile(case, wide):
     B, Hq, Hkv, Lq, Lk, D, dt, alibi, cap, win = case
     assert (Lk - Lq) % 32 == 31 if alibi else (Lk - Lq - win) % 32 == 0
-    print(f"first-tile case {case}", flush=True)
+    print(f"first-tile case {case} {wide}", flush=True)
     q, k, v = random_tensors([(B, Hq, Lq, D), (B, Hkv, Lk, D), (B, Hkv, Lk, D)], dt, seed=Lq + Lk)
     sl = alibi_slopes(Hq) if alibi else None
     kw = dict(scale=D ** -0.5, causal=True, slopes=sl, softcap=cap, window=win)
-    got, ref = host32(run_fwd(q, k, v, **kw)).astype(np.float64), oracle_fwd(q, k, v, **kw)
+    R = WIDE if wide else 1
+    if wide:
+        name = pa.attn_fwd_call_kernels(B * R, Hq, Hkv, Lq, Lk, D, q.dtype, True, alibi, cap, win)
+        assert name == [f"prefill_kernel<{D},{dt},1,{int(alibi)},{int(bool(cap))},{int(bool(win))}>"]
+    o = run_fwd(*(t.repeat(R, 1, 1, 1) for t in (q, k, v)), **kw)
+    assert all((o[b * B:(b + 1) * B] == o[:B]).all() for b in range(1, R))
+    got, ref = host32(o[:B]).astype(np.float64), oracle_fwd(q, k, v, **kw)
     row = np.linalg.norm(got - ref, axis=-1) / np.linalg.norm(ref, axis=-1)
     # P and O are each rounded to the input type: at most half an ulp per
     # value, 2^-11 (fp16) or 2^-8 (bf16), in weights and output together twice
