@@ -64,7 +64,7 @@ def unit_dir(name):
 def device_asm_files():
     """Device assembly of every kernel unit written by the last build()."""
     return prefill_asm_files() + [os.path.join(unit_dir(u), f"{u}-hip-amdgcn-amd-amdhsa-{ARCH}.s")
-                                  for u in ("decode", "peaks", "norms")]
+                                  for u in ("prefill_split", "decode", "peaks", "norms")]
 
 
 def prefill_asm_files():

@@ -12,7 +12,7 @@ import pytest
 
 import paper_2510_08726_amd as pa
 from paper_2510_08726_amd import build as libbuild
-from kernel_cases import DECODE_VARIANT_CASES, NORM_CASES, PREFILL_VARIANT_CASES
+from kernel_cases import DECODE_VARIANT_CASES, NORM_CASES, PREFILL_SPLIT_CASES, PREFILL_VARIANT_CASES, WIDE_BATCH
 
 _ARG = re.compile(r"Li(-?\d+)E|DF16_|DF16b|Lb([01])E|^f")
 
@@ -60,15 +60,18 @@ def test_every_compiled_kernel_is_exercised(compiled):
     import torch
     dt = {"f16": torch.float16, "bf16": torch.bfloat16}
     used = set()
-    for B, Hq, Hkv, Lq, Lk, D, d, causal, alibi, cap, win in PREFILL_VARIANT_CASES:
-        used.update(pa.attn_fwd_kernels(D, dt[d], causal, alibi, cap or 0.0, win or 0))
+    for B, Hq, Hkv, Lq, Lk, D, d, causal, alibi, cap, win in PREFILL_VARIANT_CASES:   # once as they are, once wide
+        for batch in (B, B * WIDE_BATCH):
+            used.update(pa.attn_fwd_call_kernels(batch, Hq, Hkv, Lq, Lk, D, dt[d], causal, alibi, cap, win))
+    for B, Hq, Hkv, Lq, Lk, D, d, causal, alibi, cap, win in PREFILL_SPLIT_CASES:
+        used.update(pa.attn_fwd_call_kernels(B, Hq, Hkv, Lq, Lk, D, dt[d], causal, alibi, cap, win))
     for B, Hq, Hkv, Lk, D, d, alibi, cap, S in DECODE_VARIANT_CASES:
         used.update(pa.attn_decode_kernels(Hq, Hkv, D, dt[d], alibi, cap or 0.0))
     ndt = {"f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}
     for N, M, d, C in NORM_CASES:   # tests/test_gpu_norms.py runs both operations on each
         for op in ("l2", "rms"):
             used.update(pa.norm_kernels(op, M, ndt[d], C or pa.norm_chunks(op, N, M, ndt[d])))
-    assert len(compiled) == 32 + 64 + 16 + 4 + 16, sorted(compiled)
+    assert len(compiled) == 32 + 24 + 4 + 64 + 16 + 4 + 16, sorted(compiled)
     assert used == compiled, (sorted(compiled - used), sorted(used - compiled))
 
 
@@ -82,3 +85,15 @@ def test_dispatch_query_rejects_what_the_entry_points_reject():
         pa.attn_fwd_kernels(128, torch.float16, 1, 1, 3.0, 0)       # SoftCap with ALiBi
     with pytest.raises(pa.AttnError):
         pa.attn_decode_kernels(6, 4, 128, torch.float16, 0)         # Hq % Hkv != 0
+
+
+def test_split_cases_cover_both_numbers_of_groups_and_ranges():
+    """Each split kernel has a case with one key range and one with several."""
+    import torch
+    dt = {"f16": torch.float16, "bf16": torch.bfloat16}
+    seen = set()
+    for B, Hq, Hkv, Lq, Lk, D, d, causal, alibi, cap, win in PREFILL_SPLIT_CASES:
+        names = pa.attn_fwd_call_kernels(B, Hq, Hkv, Lq, Lk, D, dt[d], causal, alibi, cap, win)
+        assert names[0].startswith("prefill_split_kernel"), names
+        seen.add((names[0], len(names)))
+    assert len(seen) == 2 * 24, sorted(seen)
