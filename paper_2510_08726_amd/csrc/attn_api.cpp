@@ -144,12 +144,12 @@ int attn_fwd_split(const void* Q, const void* K, const void* V, void* O,
   if (S > 1 && (workspace_bytes < attn_fwd_workspace_bytes(B, Hq, Lq, D, S) || (reinterpret_cast<uintptr_t>(workspace) & 15)))
     return ATTN_ERR_WORKSPACE;
 
-  attn::PrefillParams p{};
+  attn::PrefillSplitParams p{};
   p.q = Q; p.k = K; p.v = V; p.o = O;
   p.slopes = alibi_slopes;
   p.B = B; p.Hq = Hq; p.Hkv = Hkv; p.Lq = Lq; p.Lk = Lk; p.D = D;
   p.group = Hq / Hkv;
-  p.causal = causal ? 1 : 0;
+  p.causal = causal != 0;
   p.bf16 = dtype == ATTN_BF16;
   p.cap_k2 = softcap > 0.f ? 2.f / softcap : 0.f;
   p.cap_cl = softcap > 0.f ? softcap * kLog2e : 0.f;
@@ -167,10 +167,9 @@ int attn_fwd_split(const void* Q, const void* K, const void* V, void* O,
     p.qsign = std::signbit(scale) ? 0x80008000u : 0u;
   }
   p.nqb = (int)nqb;
-  p.kgroups = plan.kgroups;
   p.splits = S;
   p.ws = static_cast<float*>(workspace);
-  hipError_t e = attn::launch_prefill(p, stream);
+  hipError_t e = plan.kgroups > 0 ? attn::launch_prefill_split(p, plan.kgroups, stream) : attn::launch_prefill(p, stream);
   return e == hipSuccess ? ATTN_OK : hip_fail(e);
 }
 

@@ -15,8 +15,8 @@ struct PrefillParams {
   const float* slopes;  // device, [Hq], or nullptr
   int B, Hq, Hkv, Lq, Lk, D;
   int group;            // Hq / Hkv
-  int causal;
-  int bf16;
+  bool causal, bf16;
+  bool sorted;          // prefill.hip: a share's items go out heaviest first, set by the launcher
   float c;              // |scale| * log2(e) without ALiBi or SoftCap, scale * log2(e) with either
   unsigned qsign;       // 0x80008000 to negate Q (negative scale, no ALiBi or SoftCap), else 0
   float cap_k2;         // SoftCap: 2 / cap
@@ -27,10 +27,15 @@ struct PrefillParams {
   int nitems;           // nqb * nheads, set by the launcher
   int nxcd;             // shares of the items, each with its own workgroups: the XCDs, or 1; set by the launcher
   int hg;               // query heads per workgroup (sharing one KV head), set by the launcher
-  int kgroups;          // key groups of prefill_split.hip (2 or 4), 0 for prefill.hip
-  int splits;           // its key ranges (1: none)
-  float* ws;            // its partials, for splits > 1: [splits, B*Hq*Lq, D], then (max, sum) [splits, B*Hq*Lq, 2]
-  int sorted;           // 1: a share's items go out heaviest first, set by the launcher
+};
+// The kernel reads its arguments and, behind them, the grid size: within two
+// cache lines here.  (24 bytes more, and one of the next line, were 0.2 us of a
+// 25.9 us call.)
+static_assert(sizeof(PrefillParams) + 4 <= 128, "arguments and grid size within two lines");
+
+struct PrefillSplitParams : PrefillParams {
+  int splits;           // key ranges (1: none)
+  float* ws;            // partials, for splits > 1: [splits, B*Hq*Lq, D], then (max, sum) [splits, B*Hq*Lq, 2]
 };
 
 struct DecodeParams {
@@ -79,8 +84,7 @@ int prefill_block_rows();
 int prefill_order(int nitems, int nqb, int slots, bool causal, int window, int Lk, int64_t kv_bytes);
 hipError_t launch_prefill(const PrefillParams& p, hipStream_t stream);
 // Few query rows: keys split inside the workgroup, and with a workspace over
-// workgroups (prefill_split.hip); launch_prefill takes it when the plan of the
-// call says so.
+// workgroups (prefill_split.hip), where the plan of the call says so.
 constexpr int kMaxPrefillSplits = 32;
 struct PrefillSplitPlan {
   int kgroups;          // key groups of its workgroups (2 or 4), or 0: prefill.hip runs
@@ -88,7 +92,7 @@ struct PrefillSplitPlan {
 };
 PrefillSplitPlan prefill_split_plan(int B, int Hq, int Hkv, int Lq, int Lk, int D, bool causal, int window, bool alibi,
                                     bool cap, int cus, int max_splits);
-hipError_t launch_prefill_split(const PrefillParams& p, hipStream_t stream);
+hipError_t launch_prefill_split(const PrefillSplitParams& p, int kgroups, hipStream_t stream);
 // One per (head dim, element type); launch_prefill dispatches to them.
 hipError_t launch_prefill_d128_f16(const PrefillParams& p, hipStream_t stream);
 hipError_t launch_prefill_d128_bf16(const PrefillParams& p, hipStream_t stream);

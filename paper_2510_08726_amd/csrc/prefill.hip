@@ -1220,7 +1220,7 @@ hipError_t launch_t(const PrefillParams& p, hipStream_t stream) {
 
 template <int D, typename T>
 hipError_t launch_d(const PrefillParams& p, hipStream_t s) {
-  const PrefillFlags f = prefill_flags(p.causal != 0, p.slopes != nullptr, p.cap_cl != 0.f, p.window > 0);
+  const PrefillFlags f = prefill_flags(p.causal, p.slopes != nullptr, p.cap_cl != 0.f, p.window > 0);
   if (f.win) {
     if (f.cap) return launch_t<D, T, true, false, true, true>(p, s);
     return f.alibi ? launch_t<D, T, true, true, false, true>(p, s) : launch_t<D, T, true, false, false, true>(p, s);
@@ -1275,7 +1275,6 @@ int prefill_order(int nitems, int nqb, int slots, bool causal, int window, int L
 }
 
 hipError_t launch_prefill(const PrefillParams& p, hipStream_t stream) {
-  if (p.kgroups > 0) return launch_prefill_split(p, stream);
   if (p.D == 64) return p.bf16 ? launch_prefill_d64_bf16(p, stream) : launch_prefill_d64_f16(p, stream);
   return p.bf16 ? launch_prefill_d128_bf16(p, stream) : launch_prefill_d128_f16(p, stream);
 }

@@ -72,7 +72,7 @@ template <> struct RowSum<__bf16> {
 };
 
 template <int D, typename T, int G, bool ALIBI, bool CAP>
-__global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void prefill_split_kernel(PrefillParams p) {
+__global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void prefill_split_kernel(PrefillSplitParams p) {
   typedef Elem<T> E;
   typedef typename E::vec8 vec8;
   constexpr bool LOG2 = ALIBI || CAP;          // scores prepared in log2 units before the max
@@ -347,7 +347,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 4 : 2) void prefill_split_kerne
 // Global nests over the key ranges: D / 4 threads a row, kBatch ranges' loads
 // in flight at a time.
 template <int D, typename T>
-__global__ __launch_bounds__(256) void prefill_combine_kernel(PrefillParams p) {
+__global__ __launch_bounds__(256) void prefill_combine_kernel(PrefillSplitParams p) {
   constexpr int kBatch = 8, CH = D / 4;
   const size_t nr = (size_t)p.nheads * p.Lq;
   const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
@@ -390,7 +390,7 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(PrefillParams p) {
 }
 
 template <int D, typename T, int G>
-void launch_g(const PrefillParams& p, hipStream_t stream) {
+void launch_g(const PrefillSplitParams& p, hipStream_t stream) {
   const dim3 grid((p.nitems + kXcds - 1) / kXcds * kXcds), block(kThreads);
   if (p.slopes) hipLaunchKernelGGL((prefill_split_kernel<D, T, G, true, false>), grid, block, 0, stream, p);
   else if (p.cap_cl != 0.f) hipLaunchKernelGGL((prefill_split_kernel<D, T, G, false, true>), grid, block, 0, stream, p);
@@ -398,8 +398,8 @@ void launch_g(const PrefillParams& p, hipStream_t stream) {
 }
 
 template <int D, typename T>
-hipError_t launch_d(const PrefillParams& p, hipStream_t stream) {
-  if (p.kgroups == 2) launch_g<D, T, 2>(p, stream);
+hipError_t launch_d(const PrefillSplitParams& p, int kgroups, hipStream_t stream) {
+  if (kgroups == 2) launch_g<D, T, 2>(p, stream);
   else launch_g<D, T, 4>(p, stream);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.splits == 1) return e;
@@ -535,15 +535,15 @@ PrefillSplitPlan prefill_split_plan(int B, int Hq, int Hkv, int Lq, int Lk, int 
   return plan.splits == 1 && (alibi || cap) ? best(alibi, cap, 1) : plan;
 }
 
-hipError_t launch_prefill_split(const PrefillParams& p, hipStream_t stream) {
-  PrefillParams q = p;
-  q.hg = heads_per_item(p.group, kWaves / p.kgroups);
-  const int rows = 32 * (kWaves / p.kgroups / q.hg);
+hipError_t launch_prefill_split(const PrefillSplitParams& p, int kgroups, hipStream_t stream) {
+  PrefillSplitParams q = p;
+  q.hg = heads_per_item(p.group, kWaves / kgroups);
+  const int rows = 32 * (kWaves / kgroups / q.hg);
   q.nqb = (p.Lq + rows - 1) / rows;
   q.nheads = p.B * p.Hq;
   q.nitems = q.nqb * (q.nheads / q.hg) * q.splits;
-  if (p.D == 64) return p.bf16 ? launch_d<64, __bf16>(q, stream) : launch_d<64, _Float16>(q, stream);
-  return p.bf16 ? launch_d<128, __bf16>(q, stream) : launch_d<128, _Float16>(q, stream);
+  if (p.D == 64) return p.bf16 ? launch_d<64, __bf16>(q, kgroups, stream) : launch_d<64, _Float16>(q, kgroups, stream);
+  return p.bf16 ? launch_d<128, __bf16>(q, kgroups, stream) : launch_d<128, _Float16>(q, kgroups, stream);
 }
 
 }  // namespace attn
