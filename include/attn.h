@@ -41,7 +41,8 @@
  *    mutable state apart from a thread-local copy of the last HIP error.
  *  - Asynchrony: work is enqueued on `stream` and the call returns without
  *    synchronising.  Argument errors are detected on the host before
- *    anything is enqueued; in that case nothing runs and no HIP call is made.
+ *    anything is enqueued; in that case nothing runs (the current device and
+ *    its compute units may be asked for, to size a workspace).
  *  - O must not alias Q, K or V.  Each call is deterministic: the same inputs
  *    and arguments give bitwise identical outputs (no atomics).
  *  - Return value: ATTN_OK or a negative attn_status.

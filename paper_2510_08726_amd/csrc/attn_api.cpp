@@ -1,6 +1,7 @@
 // C ABI of the fused-attention library: argument validation on the host,
 // dispatch to the gfx950 kernels, error reporting.  Every check runs before
-// any HIP call, so a rejected call enqueues nothing.
+// anything is enqueued; the only HIP call among them asks for the current
+// device and its compute units, where a workspace's size depends on them.
 
 #include <algorithm>
 #include <atomic>
@@ -100,7 +101,7 @@ const char* attn_status_string(int status) {
     case ATTN_ERR_NULL: return "ATTN_ERR_NULL: a required pointer is NULL";
     case ATTN_ERR_SHAPE: return "ATTN_ERR_SHAPE: invalid sizes (need B,Hq,Hkv,Lq,Lk >= 1, Hq % Hkv == 0, num_splits >= 0, window >= 0, finite scale, finite softcap >= 0)";
     case ATTN_ERR_UNSUPPORTED: return "ATTN_ERR_UNSUPPORTED: head dim must be 64 or 128 and dtype ATTN_F16 or ATTN_BF16; softcap and window need the causal mask, softcap excludes ALiBi";
-    case ATTN_ERR_WORKSPACE: return "ATTN_ERR_WORKSPACE: decode workspace too small (attn_decode_noalloc: the split count needs more than its 16 MiB static workspace)";
+    case ATTN_ERR_WORKSPACE: return "ATTN_ERR_WORKSPACE: workspace too small or not 16-byte aligned (attn_decode_noalloc: the split count needs more than its 16 MiB static workspace)";
     case ATTN_ERR_HIP: return "ATTN_ERR_HIP: a HIP launch failed (see attn_last_hip_error)";
     default: return "unknown attn_status";
   }
@@ -383,9 +384,12 @@ int norm_chunks(int rms, int N, int M, norm_dtype dtype) {
   //    that of a second kernel (64 x 32768 bf16 RMSNorm 4.1 us, 5.9 with 8
   //    chunks; L2 64 x 16384 fp32 3.9 against 5.1; at 128 KiB 7.8 against
   //    6.7 for 64 rows);
-  //  - half the compute units have a row of at most 208 KiB, the longest
-  //    measured (RMSNorm 128 x 50000 fp32 11.9 us against 13.9, 400 x 100000
-  //    bf16 30 against 43; L2 150 x 50000 fp32 8.7 against 9.3);
+  //  - half the compute units have a row of at most 208 KiB: there the L2 norm
+  //    has its line (128 fp32 rows: 208 KiB 9.2 us against 9.4 with 4 chunks,
+  //    240 KiB 10.4 against 9.8; bf16 160 KiB 7.9 and 8.7, 208 KiB 9.9 and 9.6),
+  //    while RMSNorm gains up to what it holds (128 rows of 256 KiB 14.5 against
+  //    15.7, 200 18.4 against 28.9), which the next line takes only with more
+  //    rows;
   //  - the rows fill at least 85 % of the compute units' rounds and, for
   //    RMSNorm, a row fits the workgroup's registers (256 x 2^17: RMSNorm
   //    1.19x the two kernels with 2 chunks, the L2 norm 1.03x; but L2 300 x

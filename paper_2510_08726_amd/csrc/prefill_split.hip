@@ -17,12 +17,17 @@
 // layouts of decode.hip.  K and V tiles pass through kStages LDS buffers per
 // group, filled by buffer loads that write LDS directly.
 //
-// What bounds it: one compute unit fetches about 50 GB/s from past its XCD's
-// L2 here, 128 KB of tiles in flight at 1.3 us (more in flight, by touching
-// later tiles, was 10 % slower), so 4 groups of 16 KB a step (D = 128) take 1.2
-// us; with 2 groups the two waves of a SIMD take 0.95 us for their tiles.  Hence
-// the choice between more groups (fewer steps) and more columns per tile
-// fetched, and the key ranges over more compute units: see the plan below.
+// What bounds it: the step of a workgroup, not one unit.  With 4 groups (D =
+// 128) a step reads 64 KB of tiles while the next 64 KB are on their way, and
+// takes 1.2 us: about 55 GB/s for a compute unit, from past its XCD's L2.  Every
+// group waits for its copies with nothing else in flight, and at a barrier for
+// the slowest group.  Counters (1 x 32/8 heads, 500 rows on 6100 keys): MFMA
+// busy 0.30 of the SIMD cycles, VALU active 0.29; of a wave's cycles 0.36 wait
+// for copies, barriers and results, 0.32 for issue, 0.32 issue.  (Touching later
+// tiles ahead of their copies was 10 % slower.)  With 2 groups, four buffers and
+// three tiles in flight each, the two waves of a SIMD take 0.95 us.  Hence the
+// choice between more groups (fewer steps) and more columns per tile fetched,
+// and the key ranges over more compute units: see the plan below.
 
 #include <algorithm>
 #include <cmath>
