@@ -88,3 +88,14 @@ def test_grouped_chunks_at_head_dim_64(case):
     o = pa.attn_decode(q, k, v, workspace=ws)
     assert torch.equal(o, pa.attn_decode(q, k, v, num_splits=one))
     assert_close(host32(o), ref, f"decode {case}, {one} chunks")
+
+
+def test_output_at_any_element():
+    """O may begin at any element (the combine stores 8 bytes a lane)."""
+    q, k, v = (t.cuda() for t in random_tensors([(2, 8, 1, 64), (2, 2, 900, 64), (2, 2, 900, 64)], "f16", seed=4))
+    ref = pa.attn_decode(q, k, v, num_splits=5)
+    for shift in (1, 2, 3):
+        o = torch.zeros(q.numel() + 8, dtype=q.dtype, device="cuda")
+        part = o[shift:shift + q.numel()].view(q.shape)
+        assert torch.equal(pa.attn_decode(q, k, v, part, num_splits=5), ref)
+        assert not o[:shift].any() and not o[shift + q.numel():].any()
