@@ -505,6 +505,9 @@ __global__ __launch_bounds__(kThreads) void decode_combine_kernel(DecodeParams p
       m[u] = mp[s];
       l[u] = lp[s];
     }
+    // (Not loaded under the conditions below, one after another.)
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) asm volatile("" : "+v"(v[u]), "+v"(l[u]));
     float mn = M;
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) mn = fmaxf(mn, m[u]);
@@ -515,12 +518,13 @@ __global__ __launch_bounds__(kThreads) void decode_combine_kernel(DecodeParams p
     M = mn;
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      // A repeat is left out by its values, not by its weight: 0 times an
-      // infinite value would be NaN.
-      const bool in = s0 + u * NG < S;
-      const float w = (in && m[u] != kNegInf) ? fast_exp2((m[u] - mn) * kLog2e) : 0.f;
-      L = __builtin_fmaf(w, l[u], L);
-      acc += w * (in ? v[u] : f32x4{0.f, 0.f, 0.f, 0.f});
+      // A repeat is left out altogether: a weight of 0 times an infinite value
+      // would be NaN.
+      if (s0 + u * NG < S) {
+        const float w = m[u] != kNegInf ? fast_exp2((m[u] - mn) * kLog2e) : 0.f;
+        L = __builtin_fmaf(w, l[u], L);
+        acc += w * v[u];
+      }
     }
   }
   sh_o[g][ch] = acc;
