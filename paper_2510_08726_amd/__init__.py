@@ -212,6 +212,12 @@ def _fwd_args(q, k, v, o, alibi_slopes):
     return o
 
 
+def _on_stream(t, stream):
+    """The stream of a call, if PyTorch can allocate for it beside t, else None."""
+    s = torch.cuda.current_stream() if stream is None else stream
+    return s if isinstance(s, torch.cuda.Stream) and s.device == t.device else None
+
+
 def _fwd_workspace(q, Hkv, Lk, causal, window, stream):
     """The workspace of a call whose keys are divided over workgroups, or None
     (one range): allocated in the pool of the stream that it is used on, so
@@ -219,14 +225,23 @@ def _fwd_workspace(q, Hkv, Lk, causal, window, stream):
     B, Hq, Lq, D = q.shape
     lib = load_library()
     S = lib.attn_fwd_num_splits(B, Hq, Hkv, Lq, Lk, D, int(bool(causal)), int(window or 0))
-    s = torch.cuda.current_stream() if stream is None else stream
-    if S <= 1 or not isinstance(s, torch.cuda.Stream) or s.device != q.device:
+    s = _on_stream(q, stream)
+    if S <= 1 or s is None:
         return None
     try:
         with torch.cuda.stream(s):
             return torch.empty(lib.attn_fwd_workspace_bytes(B, Hq, Lq, D, S), dtype=torch.uint8, device=q.device)
     except torch.cuda.OutOfMemoryError:
         return None
+
+
+def _workspace(t, nbytes, stream):
+    """A workspace that a call drops when it returns, before its kernels have
+    run: in the pool of their stream, where the next tenant of the memory runs
+    after them.  (A stream of another kind, or of another device, has no such
+    pool here: the caller of one keeps its workspace itself.)"""
+    with torch.cuda.stream(_on_stream(t, stream)):
+        return torch.empty(max(nbytes, 16), dtype=torch.uint8, device=t.device)
 
 
 def attn_fwd(q, k, v, o=None, *, causal=False, scale=None, alibi_slopes=None, softcap=None,
@@ -272,7 +287,7 @@ def attn_decode_num_splits(B, Hq, Hkv, Lk, D):
     return load_library().attn_decode_num_splits(B, Hq, Hkv, Lk, D)
 
 
-def _decode_args(q, k, v, o, alibi_slopes, num_splits, workspace):
+def _decode_args(q, k, v, o, alibi_slopes, num_splits, workspace, stream):
     _check_tensors(q, k, v, alibi_slopes)
     B, Hq, Lq, D = q.shape
     _require(Lq == 1, "decode takes one query token (q.shape[2] == 1)")
@@ -286,7 +301,7 @@ def _decode_args(q, k, v, o, alibi_slopes, num_splits, workspace):
     S = num_splits if num_splits else lib.attn_decode_num_splits(B, Hq, Hkv, Lk, D)
     need = lib.attn_decode_workspace_bytes(B, Hq, D, max(S, 1))
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
+        workspace = _workspace(q, need, stream)
     return o, workspace
 
 
@@ -305,7 +320,7 @@ def attn_decode(q, k, v, o=None, *, scale=None, alibi_slopes=None, softcap=None,
     if softcap:
         return attn_decode_mod(q, k, v, o, scale=scale, alibi_slopes=alibi_slopes, softcap=softcap,
                                num_splits=num_splits, workspace=workspace, stream=stream)
-    o, workspace = _decode_args(q, k, v, o, alibi_slopes, num_splits, workspace)
+    o, workspace = _decode_args(q, k, v, o, alibi_slopes, num_splits, workspace, stream)
     B, Hq, _, D = q.shape
     Hkv, Lk = k.shape[1], k.shape[2]
     sc = 1.0 / math.sqrt(D) if scale is None else float(scale)
@@ -322,7 +337,7 @@ def attn_decode_mod(q, k, v, o=None, *, scale=None, alibi_slopes=None, softcap=N
     r = (_BINDING or _load_binding()).attn_decode(q, k, v, o, scale, alibi_slopes, softcap, num_splits, workspace, stream)
     if r is not None:
         return _result(r)
-    o, workspace = _decode_args(q, k, v, o, alibi_slopes, num_splits, workspace)
+    o, workspace = _decode_args(q, k, v, o, alibi_slopes, num_splits, workspace, stream)
     B, Hq, _, D = q.shape
     Hkv, Lk = k.shape[1], k.shape[2]
     sc = 1.0 / math.sqrt(D) if scale is None else float(scale)
@@ -437,15 +452,14 @@ def norm_workspace_bytes(N, chunks):
     return load_library().norm_workspace_bytes(N, chunks)
 
 
-def _norm_args(op, x, chunks, workspace):
+def _norm_args(op, x, chunks, workspace, stream):
     _require(x.is_cuda and x.is_contiguous() and x.dim() == 2, "x must be a contiguous 2-D GPU tensor [N, M]")
     _require(x.dtype in _NORM_CODE, "x must be float16, bfloat16 or float32")
     N, M = x.shape
     lib = load_library()
     C = chunks or lib.norm_chunks(int(op == "rms"), N, M, _NORM_CODE[x.dtype])
     if workspace is None:
-        workspace = torch.empty(max(lib.norm_workspace_bytes(N, max(C, 1)), 16), dtype=torch.uint8,
-                                device=x.device)
+        workspace = _workspace(x, lib.norm_workspace_bytes(N, max(C, 1)), stream)
     return N, M, workspace
 
 
@@ -454,7 +468,7 @@ def norm_l2(x, out=None, *, chunks=0, workspace=None, stream=None):
     r = (_BINDING or _load_binding()).norm_l2(x, out, chunks, workspace, stream)
     if r is not None:
         return _result(r)
-    N, M, workspace = _norm_args("l2", x, chunks, workspace)
+    N, M, workspace = _norm_args("l2", x, chunks, workspace, stream)
     if out is None:
         out = torch.empty(N, dtype=torch.float32, device=x.device)
     _require(out.is_cuda and out.dtype == torch.float32 and out.numel() == N, "out must be float32 [N]")
@@ -468,7 +482,7 @@ def rmsnorm_rowmax(x, y=None, rowmax=None, *, eps=1e-6, chunks=0, workspace=None
     r = (_BINDING or _load_binding()).rmsnorm_rowmax(x, y, rowmax, eps, chunks, workspace, stream)
     if r is not None:
         return _result(r)
-    N, M, workspace = _norm_args("rms", x, chunks, workspace)
+    N, M, workspace = _norm_args("rms", x, chunks, workspace, stream)
     if y is None:
         y = torch.empty_like(x)
     if rowmax is None:

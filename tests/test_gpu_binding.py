@@ -170,3 +170,28 @@ def test_key_ranges_without_memory_in_python(monkeypatch):
         _in_python(monkeypatch, lambda: pa.attn_fwd(q, k, v, o, causal=True))
     torch.cuda.synchronize()
     assert (o.float() - ref.float()).abs().max() < 2e-3 and not torch.equal(o, ref)
+
+
+def test_workspaces_belong_to_the_stream_of_the_call(monkeypatch):
+    """With stream= the workspace, which is dropped before the kernels have
+    run, comes from that stream's pool: from another one it could be handed
+    out again at once.  The results are those of plain calls."""
+    q, k, v = _qkv(Lq=1, Lk=3000, D=128)
+    x = torch.randn(8, 40000, device="cuda")
+    calls = [lambda s: pa.attn_decode(q, k, v, stream=s), lambda s: pa.attn_decode_mod(q, k, v, softcap=5.0, stream=s),
+             lambda s: pa.norm_l2(x, stream=s), lambda s: pa.rmsnorm_rowmax(x, stream=s)[0]]
+    ref = [f(None) for f in calls]
+    s, empty, seen = torch.cuda.Stream(), torch.empty, []
+
+    def record(*a, **kw):
+        if kw.get("dtype") is torch.uint8:
+            seen.append(torch.cuda.current_stream())
+        return empty(*a, **kw)
+
+    s.wait_stream(torch.cuda.current_stream())
+    with monkeypatch.context() as m:
+        m.setattr(torch, "empty", record)
+        got = [f(s) for f in calls]
+    s.synchronize()
+    assert seen == [s] * len(calls)
+    assert all(torch.equal(a, b) for a, b in zip(got, ref))
